@@ -66,14 +66,18 @@ struct FactorParams {
   int look;                        // DIAG lookahead: DIAG(i,c) is dispatched with column c - look of its step
   int sub_delay;                   // SUB(i,r,c) is dispatched with column c + sub_delay of its step (after
                                    // the last column for c + sub_delay >= T)
-  int cached;                      // 1: k-loop operand tiles are read through the L2 (line-aligned tiles only)
-  int fast;                        // 1: every k-loop operand tile takes the direct 16-byte path, device
-                                   // coherent (b and a even, L arrays 16-byte aligned, cached == 0)
+  int load;                        // how k-loop operand tiles are read (LD_*)
   long long spin_limit;
   unsigned long long* trace;  // optional: 8 words per ticket (start, k loop done, end, type | workgroup << 8,
                               // W ready (DIAG: of g-1), L(g,g-1) published (DIAG), tile factored (DIAG),
                               // end of the last blocking wait in the k loop)
 };
+
+// k-loop operand loads of a launch (factor_load).  LD_PAIR: 16 bytes per lane
+// (even leading dimensions, 16-byte aligned L arrays); LD_ODD: 4 bytes per lane
+// (any other operands); LD_LINE: through the L2 where the tuning asks for it
+// (tiles on 128-byte lines).
+enum : int { LD_PAIR = 0, LD_ODD = 1, LD_LINE = 2 };
 
 struct Task {
   int type, i, r, c;
@@ -295,12 +299,13 @@ __device__ __forceinline__ long long uni64(long long v) {
   return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// One k-loop operand tile into LDS: the direct path without its test when the
-// launch's tiles all take it (F), else the general loader.
-template <bool F>
+// One k-loop operand tile into LDS (LD_*, see FactorParams::load): one kernel
+// instance per loader, so that the k loops carry no per-tile test.
+template <int F>
 __device__ __forceinline__ void load_k(const FactorParams& p, double* dst, const OpTile& t, int tid) {
-  if constexpr (F) tile_load_lds_fast(dst, t, tid);
-  else tile_load_lds_dev(dst, t, tid, p.cached != 0);
+  if constexpr (F == LD_PAIR) tile_load_lds_fast(dst, t, tid);
+  else if constexpr (F == LD_ODD) tile_load_lds_odd(dst, t, tid);
+  else tile_load_lds_dev(dst, t, tid, p.load == LD_LINE);
 }
 
 // Block until flags are set (thread 0 polls); returns false on abort.
@@ -345,7 +350,7 @@ __device__ __forceinline__ void publish(int* flag, int tid) {
 // One k loop over the k < g-1 shared by both accumulates
 //   acc1 = -(A(g,g) - sum_k L(g,k) L(g,k)^T),  acc2 = -(A(g,g-1) - sum_k L(g,k) L(g-1,k)^T)
 // (a padded diagonal tile gets -1 on the padded diagonal).
-template <bool F>
+template <int F>
 __device__ __forceinline__ void diag_partials(const FactorParams& p, const Task& t, Shared& sh, int tid, Acc& acc1,
                                               Acc& acc2, unsigned long long* rec) {
   const int T = p.T, b = p.b;
@@ -595,7 +600,7 @@ __device__ __forceinline__ void diag_finish(const FactorParams& p, int i, int c,
   }
 }
 
-template <bool F>
+template <int F>
 __device__ __forceinline__ void run_diag(const FactorParams& p, const Task& t, Shared& sh, int tid,
                                          unsigned long long& tr1, unsigned long long* rec) {
   Acc acc1, acc2;
@@ -605,7 +610,7 @@ __device__ __forceinline__ void run_diag(const FactorParams& p, const Task& t, S
 }
 
 // One task of one matrix: accumulate, finish, publish.
-template <bool F>
+template <int F>
 __device__ __forceinline__ void run_task(const FactorParams& p, long long tk, Shared& sh, int tid) {
   {
     Task t = decode(p, tk);
@@ -803,7 +808,7 @@ __device__ __forceinline__ void run_task(const FactorParams& p, long long tk, Sh
 }
 
 // Persistent workers: take tickets until the task list is exhausted.
-template <bool F>
+template <int F>
 __device__ __forceinline__ void factor_worker(const FactorParams& p, Shared& sh) {
   const int tid = threadIdx.x;
   for (;;) {
@@ -821,9 +826,8 @@ __device__ __forceinline__ void factor_worker(const FactorParams& p, Shared& sh)
 // of another task, and every task has the CU's full register file.
 constexpr size_t SOLO_LDS_PAD = 0;
 static_assert(sizeof(Shared) > 80 * 1024, "one workgroup per CU relies on the LDS footprint");
-// F: every k-loop operand tile of the launch takes the direct load path
-// (FactorParams::fast), so the k loops carry no per-tile path test.
-template <bool F>
+// F: the k-loop loads of the launch (FactorParams::load).
+template <int F>
 __global__ __launch_bounds__(NT, 1) void factor_kernel(FactorParams p) {
   __shared__ Shared sh;
   factor_worker<F>(p, sh);
@@ -850,7 +854,7 @@ struct FactorBatchArgs {
   int* ctl;
 };
 
-template <bool F>
+template <int F>
 __global__ __launch_bounds__(NT, 1) void factor_batched_kernel(FactorBatchArgs args) {
   __shared__ Shared sh;
   const int tid = threadIdx.x;
@@ -968,13 +972,16 @@ static bool factor_lines_aligned(int64_t b, int64_t a, const double* LD, const d
   return b % 16 == 0 && (a == 0 || a % 16 == 0) && al(LD) && al(LB) && al(LR) && al(LT);
 }
 
-// Whether every k-loop operand tile of a factorization takes the direct
-// 16-byte load path: even b and a (even leading dimensions and column counts)
-// and 16-byte aligned L arrays.
-static bool factor_ops_direct(int64_t b, int64_t a, const double* LD, const double* LB, const double* LR,
-                              const double* LT) {
+// How a factorization reads its k-loop operand tiles: through the L2 where the
+// tuning asks for it and the tiles lie on lines, else in 16-byte pieces where
+// every tile allows it (even leading dimensions, 16-byte aligned L arrays; the
+// tip's own tiles are k-loop operands only when it has more than one), else 4
+// bytes per lane.
+static int factor_load(int64_t b, int64_t a, const double* LD, const double* LB, const double* LR, const double* LT) {
+  if (factor_cached_loads(b, a) && factor_lines_aligned(b, a, LD, LB, LR, LT)) return LD_LINE;
   auto al = [](const void* q) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  return b % 2 == 0 && a % 2 == 0 && al(LD) && al(LB) && al(LR) && al(LT);
+  const bool tip = a <= 64 || (a % 2 == 0 && al(LT));
+  return (b % 2 == 0 && tip && al(LD) && al(LB) && al(LR)) ? LD_PAIR : LD_ODD;
 }
 
 FactorPlan factor_plan(int64_t n, int64_t b, int64_t a) {
@@ -1021,8 +1028,7 @@ hipError_t factor_launch(const FactorPlan& fp, int64_t n, int64_t b, int64_t a,
   p.step_last = fp.step_last;
   p.look = fp.look;
   p.sub_delay = fp.sub_delay;
-  p.cached = (factor_cached_loads(b, a) && factor_lines_aligned(b, a, LD, LB, LR, LT)) ? 1 : 0;
-  p.fast = (!p.cached && factor_ops_direct(b, a, LD, LB, LR, LT)) ? 1 : 0;
+  p.load = factor_load(b, a, LD, LB, LR, LT);
   p.trace = trace;
   p.spin_limit = 1LL << 22;  // a few seconds of polling without progress before the watchdog fires
   const int rgrid = (int)std::min<long long>(1024, (fp.nflags + 255) / 256 + 1);
@@ -1034,10 +1040,8 @@ hipError_t factor_launch(const FactorPlan& fp, int64_t n, int64_t b, int64_t a,
   const long long grid = std::min<long long>(fp.ntasks, cap);
   if (grid < fp.ntasks && grid <= fp.look + 1) return hipErrorInvalidConfiguration;  // lookahead needs more workers
   timing_mark(KT_FACTOR, true, stream);
-  if (p.fast)
-    hipLaunchKernelGGL(factor_kernel<true>, dim3((unsigned)grid), dim3(NT), SOLO_LDS_PAD, stream, p);
-  else
-    hipLaunchKernelGGL(factor_kernel<false>, dim3((unsigned)grid), dim3(NT), SOLO_LDS_PAD, stream, p);
+  auto kernel = p.load == LD_PAIR ? factor_kernel<LD_PAIR> : p.load == LD_ODD ? factor_kernel<LD_ODD> : factor_kernel<LD_LINE>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NT), SOLO_LDS_PAD, stream, p);
   timing_mark(KT_FACTOR, false, stream);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1217,8 +1221,7 @@ hipError_t factor_batch_launch(const FactorBatchPlan& bp, const BatchMatrix* mat
     p.look = fp.look;
     p.sub_delay = fp.sub_delay;
     p.spin_limit = 1LL << 22;
-    p.cached = (factor_cached_loads(p.b, p.a) && factor_lines_aligned(p.b, p.a, p.LD, p.LB, p.LR, p.LT)) ? 1 : 0;
-    p.fast = (!p.cached && factor_ops_direct(p.b, p.a, p.LD, p.LB, p.LR, p.LT)) ? 1 : 0;
+    p.load = factor_load(p.b, p.a, p.LD, p.LB, p.LR, p.LT);
     p.trace = nullptr;
   }
   std::vector<int64_t> ns(bp.count);
@@ -1243,12 +1246,13 @@ hipError_t factor_batch_launch(const FactorBatchPlan& bp, const BatchMatrix* mat
   const long long grid = std::min<long long>(t, (long long)num_cus);
   if (grid < t && grid <= batch_ahead_bound(bp)) return hipErrorInvalidConfiguration;  // lookahead needs more workers
   timing_mark(KT_FACTOR, true, stream);
-  bool all_fast = true;
-  for (const FactorParams& q : hp) all_fast = all_fast && q.fast != 0;
-  if (all_fast)
-    hipLaunchKernelGGL(factor_batched_kernel<true>, dim3((unsigned)grid), dim3(NT), SOLO_LDS_PAD, stream, args);
-  else
-    hipLaunchKernelGGL(factor_batched_kernel<false>, dim3((unsigned)grid), dim3(NT), SOLO_LDS_PAD, stream, args);
+  // the widest loads that every matrix allows (4-byte ones suit any operands)
+  int load = LD_PAIR;
+  for (const FactorParams& q : hp) load = std::max(load, q.load);
+  auto kernel = load == LD_PAIR   ? factor_batched_kernel<LD_PAIR>
+                : load == LD_ODD ? factor_batched_kernel<LD_ODD>
+                                 : factor_batched_kernel<LD_LINE>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NT), SOLO_LDS_PAD, stream, args);
   timing_mark(KT_FACTOR, false, stream);
   e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -73,6 +73,14 @@ def test_factor_selinv_parity(torch_cuda, n, b, a):
     _check(Lg, Xg, F, Xo, n, b, a)
 
 
+@pytest.mark.parametrize("n,b,a", [(1, 1, 1), (2, 63, 1), (2, 65, 3), (2, 127, 65), (3, 129, 0), (2, 191, 129), (2, 128, 129),
+                                   (3, 320, 1)])
+def test_odd_extents(torch_cuda, n, b, a):
+    """Odd b or a: the 4-byte operand loads (and, for an even b with an odd tip
+    of one tile, the 16-byte ones), at the edges of the 64-tiles."""
+    test_factor_selinv_parity(torch_cuda, n, b, a)
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("n,b,a", [(3, 384, 6), (2, 520, 8), (4, 136, 2), (2, 64, 130), (5, 192, 0)])
 def test_selinv_gemm_kernels(torch_cuda, n, b, a, mode):
