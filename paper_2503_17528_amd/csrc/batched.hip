@@ -98,6 +98,7 @@ struct StageExec {
   long long work;   // trinv: workgroups; gemm: 64-tile count
   long long work2;  // gemm: 128-tile count
   bool pure;        // gemm: outputs do not feed the stage's inputs (safe to run twice)
+  bool pairs;       // gemm: every problem's operands take 16-byte loads
   bool skinny;      // gemm: every problem takes the skinny kernel (at most 16 rows: the arrow rows)
   std::string shape;
 };
@@ -187,6 +188,8 @@ MergedPlan build_plan(const StageRecorder& rec) {
       ex.pure = stage_pure(st.gemms);
       long long v = 0;
       ex.skinny = !(env_int("BTA_BATCH_SKINNY", 0, 1, &v) && v == 0);  // measurement override
+      ex.pairs = true;
+      for (const GProb& q : st.gemms) ex.pairs = ex.pairs && dl_ok(q);
       for (const GProb& q : st.gemms) ex.skinny = ex.skinny && gemm_skinny_ok(q);
       ex.shape = shape_key(st.gemms);
       mp.stages.push_back(ex);
@@ -255,9 +258,10 @@ hipError_t launch_stage(const StageExec& ex, char* dtab, int big, hipStream_t s)
                                        reinterpret_cast<const long long*>(dtab + ex.off_pre), ex.count, ex.work, s);
       if (big)
         return gemm_list_launch(reinterpret_cast<const GProb*>(dtab + ex.off_p128),
-                                reinterpret_cast<const long long*>(dtab + ex.off_pre128), ex.count, ex.work2, 1, s);
+                                reinterpret_cast<const long long*>(dtab + ex.off_pre128), ex.count, ex.work2, 1,
+                                ex.pairs, s);
       return gemm_list_launch(reinterpret_cast<const GProb*>(dtab + ex.off), reinterpret_cast<const long long*>(dtab + ex.off_pre),
-                              ex.count, ex.work, 0, s);
+                              ex.count, ex.work, 0, ex.pairs, s);
     }
     case 1:
       hipLaunchKernelGGL(fill_list_kernel, dim3(64, (unsigned)ex.count), dim3(256), 0, s, reinterpret_cast<const FillOp*>(dtab + ex.off));

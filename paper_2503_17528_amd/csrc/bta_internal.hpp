@@ -273,9 +273,11 @@ inline void set_stage(int phase, int major, int minor) {
 }
 inline bool recording() { return g_dry != nullptr || g_rec != nullptr; }
 
-// problem-list GEMM launch (device-resident problem array and tile prefix)
+// problem-list GEMM launch (device-resident problem array and tile prefix);
+// pairs: every problem passes dl_ok (16-byte operand loads)
 hipError_t gemm_list_launch(const GProb* d_probs, const long long* d_tile_begin, int nprob, long long ntiles, int big,
-                            hipStream_t stream);
+                            bool pairs, hipStream_t stream);
+bool dl_ok(const GProb& p);
 long long gemm_prob_tiles(GProb& p, int tile);
 // Products of at most 16 rows with plain k ranges, A by rows, B by k rows, one
 // batch entry and a full store; launched one workgroup per 64 columns

@@ -96,8 +96,8 @@ BTA_TESTING_API int bta_internal_tune_load(const char* path);
 BTA_TESTING_API int bta_internal_tune_clear(void);
 
 /* ---- GEMM engine and measurement (gemm.hip) */
-/* GEMM kernel family of the selected inversion (0 automatic, 1 register-staged,
- * 2 direct-to-LDS where allowed, 3..7 one direct-to-LDS body); returns the
+/* GEMM kernel family of the selected inversion (0 automatic, 1 4-byte operand
+ * loads, 2 16-byte ones where allowed, 3, 5 64 x 64 and 4, 6, 7 128 x 128 tiles); returns the
  * previous mode (-1 only queries). */
 BTA_TESTING_API int bta_internal_gemm_mode(int mode);
 /* One product through the grouped GEMM: C = beta*Cin + alpha*sum_k A(m,k) B(c,k). */

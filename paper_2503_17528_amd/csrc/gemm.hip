@@ -17,232 +17,10 @@
 
 namespace bta {
 
-// Tile configuration: a workgroup of 4 waves (2 x 2) computes a
-// (32*WM) x (32*WN) tile; each wave WM x WN MFMA blocks of 16 x 16; k is staged
-// through LDS in chunks of BK (row stride BK + 2 doubles: consecutive rows
-// shift by 4 banks and rows stay 16-byte aligned).
-template <int WM, int WN, int BK>
-struct GemmCfg {
-  static constexpr int TM = 32 * WM, TN = 32 * WN, LD = BK + 2;
-  static constexpr int EA = TM * BK / NT, EB = TN * BK / NT;  // doubles staged per thread
-  static_assert(EA == 16 && EB == 16, "staging assumes 16 doubles per thread per operand");
-};
-
-template <int TM, int BK>
-struct Chunk {
-  double v[16];
-};
-
-// Load one TM x BK operand chunk (element (m, k) = trans ? p[k*ld + m] : p[m*ld + k];
-// zero outside mext x kext) into registers.
-template <int TM, int BK>
-__device__ __forceinline__ void chunk_load(Chunk<TM, BK>& c, const double* p, int64_t ld, int trans, int mext, int kext,
-                                           int tid) {
-  if (!trans) {
-    constexpr int TPR = BK / 16;  // threads per row
-    const int m = tid / TPR, k0 = (tid % TPR) * 16;
-    const double* src = p + (int64_t)m * ld + k0;
-    const bool row_ok = m < mext;
-    if (row_ok && k0 + 16 <= kext && ((ld & 1) == 0) && ((((uintptr_t)src) & 15) == 0)) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        d2v x = *reinterpret_cast<const d2v*>(src + 2 * j);
-        c.v[2 * j] = x[0];
-        c.v[2 * j + 1] = x[1];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 16; ++j) c.v[j] = (row_ok && k0 + j < kext) ? src[j] : 0.0;
-    }
-  } else {
-    constexpr int TPK = TM / 16;  // threads per k row
-    const int k = tid / TPK, m0 = (tid % TPK) * 16;
-    const double* src = p + (int64_t)k * ld + m0;
-    const bool k_ok = k < kext;
-    if (k_ok && m0 + 16 <= mext && ((ld & 1) == 0) && ((((uintptr_t)src) & 15) == 0)) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        d2v x = *reinterpret_cast<const d2v*>(src + 2 * j);
-        c.v[2 * j] = x[0];
-        c.v[2 * j + 1] = x[1];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 16; ++j) c.v[j] = (k_ok && m0 + j < mext) ? src[j] : 0.0;
-    }
-  }
-}
-
-template <int TM, int BK>
-__device__ __forceinline__ void chunk_store(const Chunk<TM, BK>& c, double* lds, int trans, int tid) {
-  constexpr int LD = BK + 2;
-  if (!trans) {
-    constexpr int TPR = BK / 16;
-    const int m = tid / TPR, k0 = (tid % TPR) * 16;
-    double* dst = lds + m * LD + k0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) *reinterpret_cast<d2v*>(dst + 2 * j) = d2v{c.v[2 * j], c.v[2 * j + 1]};
-  } else {
-    constexpr int TPK = TM / 16;
-    const int k = tid / TPK, m0 = (tid % TPK) * 16;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) lds[(m0 + j) * LD + k] = c.v[j];
-  }
-}
-
 template <int WM, int WN>
 struct AccT {
   d4 v[WM][WN];
 };
-
-// acc += A_lds B_lds^T over one BK chunk (k permuted within each 16-wide group
-// so that every lane reads 4 consecutive k with two 16-byte LDS reads).
-template <int WM, int WN, int BK>
-__device__ __forceinline__ void chunk_mma(AccT<WM, WN>& acc, const double* As, const double* Bs, int tid) {
-  constexpr int LD = BK + 2;
-  const int w = tid >> 6, lane = tid & 63;
-  const int r0 = 16 * WM * (w >> 1) + (lane & 15);
-  const int c0 = 16 * WN * (w & 1) + (lane & 15);
-  const int kl = (lane >> 4) * 4;
-#pragma unroll
-  for (int kg = 0; kg < BK / 16; ++kg) {
-    d4 a[WM], b[WN];
-#pragma unroll
-    for (int i = 0; i < WM; ++i) {
-      const double* pa = As + (r0 + 16 * i) * LD + kg * 16 + kl;
-      const d2v x0 = *reinterpret_cast<const d2v*>(pa);
-      const d2v x1 = *reinterpret_cast<const d2v*>(pa + 2);
-      a[i] = d4{x0[0], x0[1], x1[0], x1[1]};
-    }
-#pragma unroll
-    for (int j = 0; j < WN; ++j) {
-      const double* pb = Bs + (c0 + 16 * j) * LD + kg * 16 + kl;
-      const d2v x0 = *reinterpret_cast<const d2v*>(pb);
-      const d2v x1 = *reinterpret_cast<const d2v*>(pb + 2);
-      b[j] = d4{x0[0], x0[1], x1[0], x1[1]};
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j) acc.v[i][j] = mfma16(a[i][s], b[j][s], acc.v[i][j]);
-  }
-}
-
-template <int WM, int WN, int BK>
-__device__ __forceinline__ void gemm_tile_body(const GProb& P, long long local, int tid, double* As, double* Bs) {
-  using C = GemmCfg<WM, WN, BK>;
-  constexpr int TM = C::TM, TN = C::TN;
-  const int batch = (int)(local / P.tiles_per_batch);
-  const int tile = (int)(local - (long long)batch * P.tiles_per_batch);
-  const int b0 = batch / P.nb1, b1 = batch - b0 * P.nb1;
-  int tm, tn;
-  if (P.lower_tiles) {
-    // tile -> (tm, tn) over the tiles that touch the lower triangle, row by row:
-    // row tm holds tiles tn = 0 .. floor((tm*TM + TM - 1) / TN)
-    tm = 0;
-    int rem = tile;
-    for (;;) {
-      const int w = min(P.ntn, (tm * TM + TM - 1) / TN + 1);
-      if (rem < w) break;
-      rem -= w;
-      ++tm;
-    }
-    tn = rem;
-  } else {
-    tm = tile / P.ntn;
-    tn = tile - tm * P.ntn;
-  }
-  const int m0 = tm * TM, n0 = tn * TN;
-  const int mext = min(TM, P.M - m0), next = min(TN, P.N - n0);
-
-  // k ranges of the segments (triangular operands clip them)
-  int kbeg[2] = {0, 0}, kend[2] = {0, 0}, nk[2] = {0, 0};
-  const double* Ab[2] = {nullptr, nullptr};
-  const double* Bb[2] = {nullptr, nullptr};
-  for (int s = 0; s < P.nseg; ++s) {
-    const GSeg& g = P.seg[s];
-    int k0 = 0, k1 = g.K;
-    switch (g.tri) {
-      case TRI_K_GE_COL: k0 = n0; break;
-      case TRI_K_GE_ROW: k0 = m0; break;
-      case TRI_K_LE_ROW: k1 = min(g.K, m0 + TM); break;
-      case TRI_K_LE_COL: k1 = min(g.K, n0 + TN); break;
-      default: break;
-    }
-    k0 = (k0 / BK) * BK;
-    if (k0 > k1) k0 = k1;
-    kbeg[s] = k0;
-    kend[s] = k1;
-    nk[s] = (k1 - k0 + BK - 1) / BK;
-    Ab[s] = g.A + b0 * g.sA0 + b1 * g.sA1;
-    Bb[s] = g.B + b0 * g.sB0 + b1 * g.sB1;
-  }
-  const int total = nk[0] + nk[1];
-
-  AccT<WM, WN> acc;
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < WN; ++jj) acc.v[i][jj] = d4{0.0, 0.0, 0.0, 0.0};
-  Chunk<TM, BK> ra;
-  Chunk<TN, BK> rb;
-  auto load = [&](int kk) {
-    const int s = kk < nk[0] ? 0 : 1;
-    const int q = s == 0 ? kk : kk - nk[0];
-    const int k = kbeg[s] + q * BK;
-    const int kext = min(BK, kend[s] - k);
-    const GSeg& g = P.seg[s];
-    const double* pa = g.at ? Ab[s] + (int64_t)k * g.lda + m0 : Ab[s] + (int64_t)m0 * g.lda + k;
-    const double* pb = g.bt ? Bb[s] + (int64_t)k * g.ldb + n0 : Bb[s] + (int64_t)n0 * g.ldb + k;
-    chunk_load<TM, BK>(ra, pa, g.lda, g.at, mext, kext, tid);
-    chunk_load<TN, BK>(rb, pb, g.ldb, g.bt, next, kext, tid);
-  };
-  if (total > 0) load(0);
-  for (int kk = 0; kk < total; ++kk) {
-    const int s = kk < nk[0] ? 0 : 1;
-    __syncthreads();
-    chunk_store<TM, BK>(ra, As, P.seg[s].at, tid);
-    chunk_store<TN, BK>(rb, Bs, P.seg[s].bt, tid);
-    __syncthreads();
-    if (kk + 1 < total) load(kk + 1);
-    chunk_mma<WM, WN, BK>(acc, As, Bs, tid);
-  }
-
-  // epilogue: final values first (Cin may alias Cout), then the stores
-  const int w = tid >> 6, lane = tid & 63;
-  const int rw = 16 * WM * (w >> 1), cw = 16 * WN * (w & 1);
-  const int64_t coff = b0 * P.sC0 + b1 * P.sC1;
-  double* Cb = P.Cout + coff;
-  const double* Cib = P.Cin ? P.Cin + coff : nullptr;
-#pragma unroll
-  for (int bi = 0; bi < WM; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < WN; ++bj)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = rw + 16 * bi + acc_row(lane, e), c = cw + 16 * bj + acc_col(lane);
-        const int gr = m0 + r, gc = n0 + c;
-        double v = P.alpha * acc.v[bi][bj][e];
-        const bool live = r < mext && c < next && !(P.store != ST_FULL && gc > gr);
-        if (live && P.beta != 0.0) v += P.beta * Cib[(int64_t)gr * P.ldc + gc];
-        acc.v[bi][bj][e] = v;
-      }
-#pragma unroll
-  for (int bi = 0; bi < WM; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < WN; ++bj)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = rw + 16 * bi + acc_row(lane, e), c = cw + 16 * bj + acc_col(lane);
-        const int gr = m0 + r, gc = n0 + c;
-        if (r >= mext || c >= next) continue;
-        if (P.store != ST_FULL && gc > gr) continue;
-        Cb[(int64_t)gr * P.ldc + gc] = acc.v[bi][bj][e];
-        if (P.store == ST_LOWER_MIRROR && gc < gr) Cb[(int64_t)gc * P.ldc + gr] = acc.v[bi][bj][e];
-      }
-}
 
 // ---------------------------------------------------------------- direct-to-LDS tile body
 // The same product with operands moved from global memory straight into LDS
@@ -266,32 +44,69 @@ __device__ __forceinline__ void load_piece_lds(const double* src, double* lds_wa
                                    (__attribute__((address_space(3))) void*)(lds_wave), 16, 0, 0);
 }
 
-template <int WM, int WN>
-struct DLCfg {
-  static constexpr int TM = 32 * WM, TN = 32 * WN, BK = 16;
-  static constexpr int SA = TM * BK, SB = TN * BK;          // doubles per stage and operand
-  static constexpr int IA = SA / 2 / NT, IB = SB / 2 / NT;  // pieces per thread per stage
-  static constexpr int STAGE = SA + SB;
-  static_assert(IA >= 1 && IB >= 1, "tile too small for the direct-load stage");
-};
-
-// One operand's pieces of stage (k .. k+kext) for the tile at row r0 (mext rows).
-template <int TR, int NI>
-__device__ __forceinline__ void stage_operand(const double* base, int64_t ld, int trans, int r0, int rext, int k,
-                                              int kext, double* dst, int wave, int lane) {
+// The same pieces with every address one lane offset past a scalar row base
+// (no per-piece pointer registers: the 64 x 64 kernels fit four waves a SIMD
+// instead of two).  BYTES 16: a piece per lane.  BYTES 4: four lanes a piece,
+// from operands at any 8-byte alignment (odd leading dimensions, where a
+// 16-byte load would need every row on a 16-byte line).  Wave w of the operand
+// fills slots SPI NI w .. SPI NI (w + 1) - 1, SPI per instruction; the rows of
+// an instruction are wave-uniform but for the lane's part, and the swizzle is
+// an xor of the lane's offset with a constant.
+template <int TR, int NI, int BYTES>
+__device__ __forceinline__ void stage_pieces(const double* base, int64_t ld, int trans, int r0, int rext, int k, int kext,
+                                             double* dst, int w, int lane) {
+  constexpr int LPP = 16 / BYTES, SPI = 64 / LPP;
+  const int slot = lane / LPP;
+  const unsigned part = BYTES * (unsigned)(lane % LPP);
+  double* const d0 = dst + w * NI * SPI * 2;
+  const bool full = rext >= TR && kext >= 16;
+  auto load = [&](const char* src, int i) {
+    auto* const to = (__attribute__((address_space(3))) void*)(d0 + 2 * SPI * i);
+    if constexpr (BYTES == 16) __builtin_amdgcn_global_load_lds(src, to, 16, 0, 0);
+    else __builtin_amdgcn_global_load_lds(src, to, 4, 0, 0);
+  };
+  const char* const zero = reinterpret_cast<const char*>(g_zero_piece);
+  if (!trans) {
+    // rows m = mw + RPI i + h, piece (slot % 8) ^ swzN(m)
+    constexpr int RPI = SPI / 8;
+    const int h = slot >> 3, mw = RPI * NI * w;
+    const unsigned x0 = 16u * ((slot & 7) ^ h ^ swzN(mw)) + part, hoff = h * (unsigned)(8 * ld);
+    const char* row = reinterpret_cast<const char*>(base + (int64_t)(r0 + mw) * ld + k);
+    if (full) {
 #pragma unroll
-  for (int j = 0; j < NI; ++j) {
-    const int slot = (wave * NI + j) * 64 + lane;
-    const double* src = g_zero_piece;
-    if (!trans) {
-      const int m = slot >> 3, p = (slot & 7) ^ swzN(slot >> 3);
-      if (m < rext && 2 * p < kext) src = base + (int64_t)(r0 + m) * ld + k + 2 * p;
+      for (int i = 0; i < NI; ++i) {
+        load(row + (hoff + (x0 ^ (16u * swzN(RPI * i)))), i);
+        row += 8 * RPI * ld;
+      }
     } else {
-      constexpr int PR = TR / 2;
-      const int kk = slot / PR, q = (slot % PR) ^ swzT(slot / PR);
-      if (kk < kext && 2 * q < rext) src = base + (int64_t)(k + kk) * ld + r0 + 2 * q;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const unsigned x = x0 ^ (16u * swzN(RPI * i));
+        load(mw + RPI * i + h < rext && (int)(x >> 3) < kext ? row + (hoff + x) : zero, i);
+        row += 8 * RPI * ld;
+      }
     }
-    load_piece_lds(src, dst + (wave * NI + j) * 128);
+  } else {
+    // k rows kk = kw + SPI i / PR + h, piece (SPI i + slot) % PR ^ swzT(kk)
+    constexpr int PR = TR / 2, RPI = SPI > PR ? SPI / PR : 1, IPR = SPI > PR ? 1 : PR / SPI;
+    const int h = slot / PR, kw = w * (NI * SPI / PR);
+    const unsigned x0 = 16u * (slot % PR) + part, hoff = h * (unsigned)(8 * ld);
+    const char* row = reinterpret_cast<const char*>(base + (int64_t)(k + kw) * ld + r0);
+    if (full) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        load(row + (hoff + (x0 ^ (16u * swzT(kw + i * SPI / PR))) + 16u * (i % IPR * SPI)), i);
+        if (i % IPR == IPR - 1) row += 8 * RPI * ld;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int kk = kw + i * SPI / PR;
+        const unsigned x = (x0 ^ (16u * swzT(kk))) + 16u * (i % IPR * SPI);
+        load(kk + h < kext && (int)(x >> 3) < rext ? row + (hoff + x) : zero, i);
+        if (i % IPR == IPR - 1) row += 8 * RPI * ld;
+      }
+    }
   }
 }
 
@@ -346,152 +161,12 @@ __device__ __forceinline__ void tile_coords(const GProb& P, int tile, int& tm, i
   }
 }
 
-// L0: layout of every problem's first segment as at * 2 + bt when the launch
-// shares one (its k loop then has no layout branch), 4 when it does not.
-template <int WM, int WN, int L0>
-__device__ __forceinline__ void gemm_tile_dl(const GProb& P, long long local, int tid, double* lds) {
-  using C = DLCfg<WM, WN>;
-  constexpr int TM = C::TM, TN = C::TN, BK = C::BK;
-  const int batch = (int)(local / P.tiles_per_batch);
-  const int tile = (int)(local - (long long)batch * P.tiles_per_batch);
-  const int b0 = batch / P.nb1, b1 = batch - b0 * P.nb1;
-  int tm, tn;
-  tile_coords<TM, TN>(P, tile, tm, tn);
-  const int m0 = tm * TM, n0 = tn * TN;
-  const int mext = min(TM, P.M - m0), next = min(TN, P.N - n0);
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-
-  // k ranges of the two segments (triangular operands clip them); plain
-  // scalars and selects, so that nothing is indexed by a run-time segment number
-  auto krange = [&](const GSeg& g, int& k0, int& k1) {
-    k0 = 0;
-    k1 = g.K;
-    switch (g.tri) {
-      case TRI_K_GE_COL: k0 = n0; break;
-      case TRI_K_GE_ROW: k0 = m0; break;
-      case TRI_K_LE_ROW: k1 = min(g.K, m0 + TM); break;
-      case TRI_K_LE_COL: k1 = min(g.K, n0 + TN); break;
-      default: break;
-    }
-    k0 = (k0 / BK) * BK;
-    if (k0 > k1) k0 = k1;
-  };
-  int kb0, ke0, kb1 = 0, ke1 = 0;
-  krange(P.seg[0], kb0, ke0);
-  if (P.nseg > 1) krange(P.seg[1], kb1, ke1);
-  const int nk0 = (ke0 - kb0 + BK - 1) / BK;
-  const int total = nk0 + (ke1 - kb1 + BK - 1) / BK;
-  const double* A0 = P.seg[0].A + b0 * P.seg[0].sA0 + b1 * P.seg[0].sA1;
-  const double* B0 = P.seg[0].B + b0 * P.seg[0].sB0 + b1 * P.seg[0].sB1;
-  const double* A1 = P.seg[1].A + b0 * P.seg[1].sA0 + b1 * P.seg[1].sA1;
-  const double* B1 = P.seg[1].B + b0 * P.seg[1].sB0 + b1 * P.seg[1].sB1;
-  // the segments' layouts and strides, read once into scalar registers (a
-  // reload inside the k loop costs a scalar load and a full wait per stage)
-  const int at0 = __builtin_amdgcn_readfirstlane(P.seg[0].at), bt0 = __builtin_amdgcn_readfirstlane(P.seg[0].bt);
-  const int at1 = __builtin_amdgcn_readfirstlane(P.seg[1].at), bt1 = __builtin_amdgcn_readfirstlane(P.seg[1].bt);
-  const int64_t lda0 = P.seg[0].lda, lda1 = P.seg[1].lda, ldb0 = P.seg[0].ldb, ldb1 = P.seg[1].ldb;
-
-  auto issue = [&](int kk) {
-    const bool first = kk < nk0;
-    const int k = first ? kb0 + kk * BK : kb1 + (kk - nk0) * BK;
-    const int kext = min(BK, (first ? ke0 : ke1) - k);
-    double* st = lds + (kk & 1) * C::STAGE;
-    stage_operand<TM, C::IA>(first ? A0 : A1, first ? lda0 : lda1, first ? at0 : at1, m0, mext, k, kext, st, wave, lane);
-    stage_operand<TN, C::IB>(first ? B0 : B1, first ? ldb0 : ldb1, first ? bt0 : bt1, n0, next, k, kext, st + C::SA,
-                             wave, lane);
-  };
-
-  AccT<WM, WN> acc;
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < WN; ++jj) acc.v[i][jj] = d4{0.0, 0.0, 0.0, 0.0};
-  const int rw = 16 * WM * (wave >> 1), cw = 16 * WN * (wave & 1);
-  // MFMA blocks with no element inside the tile's extent, or (lower stores)
-  // entirely above the diagonal, are not computed
-  bool live[WM][WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < WN; ++jj)
-      live[i][jj] = (rw + 16 * i < mext) && (cw + 16 * jj < next) &&
-                    (P.store == ST_FULL || n0 + cw + 16 * jj <= m0 + rw + 16 * i + 15);
-  bool all_live = true;
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int jj = 0; jj < WN; ++jj) all_live = all_live && live[i][jj];
-  if (total > 0) issue(0);
-  // stages [k0, k1); layout code LC < 4 fixes both operand layouts at compile time
-  auto kloop = [&](auto checked, auto lc, int k0, int k1) {
-    constexpr bool CK = decltype(checked)::value;
-    constexpr int LC = decltype(lc)::value;
-    for (int kk = k0; kk < k1; ++kk) {
-      // stage kk has landed for every wave, and every wave is done with stage kk-1
-      __syncthreads();
-      const bool first = kk < nk0;
-      const double* st = lds + (kk & 1) * C::STAGE;
-      // the next stage's loads first (its buffer was last read before the
-      // barrier), then this stage's operands
-      if (kk + 1 < total) issue(kk + 1);
-      double a[WM][4], b[WN][4];
-      stage_read<TM, WM>(a, st, LC < 4 ? (LC >> 1) : (first ? at0 : at1), rw, lane);
-      stage_read<TN, WN>(b, st + C::SA, LC < 4 ? (LC & 1) : (first ? bt0 : bt1), cw, lane);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < WM; ++i)
-#pragma unroll
-          for (int jj = 0; jj < WN; ++jj)
-            if (!CK || live[i][jj]) acc.v[i][jj] = mfma16(a[i][q], b[jj][q], acc.v[i][jj]);
-    }
-  };
-  using LFix = std::integral_constant<int, L0>;
-  using LRun = std::integral_constant<int, 4>;
-  if (__builtin_amdgcn_readfirstlane((int)all_live)) {
-    kloop(std::false_type{}, LFix{}, 0, L0 < 4 ? nk0 : total);
-    if (L0 < 4) kloop(std::false_type{}, LRun{}, nk0, total);
-  } else {
-    kloop(std::true_type{}, LFix{}, 0, L0 < 4 ? nk0 : total);
-    if (L0 < 4) kloop(std::true_type{}, LRun{}, nk0, total);
-  }
-
-  const int64_t coff = b0 * P.sC0 + b1 * P.sC1;
-  double* Cb = P.Cout + coff;
-  const double* Cib = P.Cin ? P.Cin + coff : nullptr;
-#pragma unroll
-  for (int bi = 0; bi < WM; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < WN; ++bj)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = rw + 16 * bi + acc_row(lane, e), c = cw + 16 * bj + acc_col(lane);
-        const int gr = m0 + r, gc = n0 + c;
-        double v = P.alpha * acc.v[bi][bj][e];
-        const bool live = r < mext && c < next && !(P.store != ST_FULL && gc > gr);
-        if (live && P.beta != 0.0) v += P.beta * Cib[(int64_t)gr * P.ldc + gc];
-        acc.v[bi][bj][e] = v;
-      }
-#pragma unroll
-  for (int bi = 0; bi < WM; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < WN; ++bj)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = rw + 16 * bi + acc_row(lane, e), c = cw + 16 * bj + acc_col(lane);
-        const int gr = m0 + r, gc = n0 + c;
-        if (r >= mext || c >= next) continue;
-        if (P.store != ST_FULL && gc > gr) continue;
-        Cb[(int64_t)gr * P.ldc + gc] = acc.v[bi][bj][e];
-        if (P.store == ST_LOWER_MIRROR && gc < gr) Cb[(int64_t)gc * P.ldc + gr] = acc.v[bi][bj][e];
-      }
-}
-
 // ---------------------------------------------------------------- lean direct-to-LDS tile body
 // Waves WR x WC, each (16 BI) x (16 BJ) of the (16 BI WR) x (16 BJ WC) tile;
-// stages of BK = 16 as in gemm_tile_dl (same piece layouts).  The source of
-// each of a thread's pieces is resolved once per segment (pointer, validity,
-// k position); a stage only advances the pointers.
+// stages of BK = 16 as in gemm_tile_dl (same piece layouts).  The loads of 64 x
+// 64 tiles and of U go through stage_pieces; those of 128 x 128 tiles keep a
+// pointer per piece (registers are free there, one workgroup per CU, and the
+// scalar row bases measured slower: n=32, b=4096 321.9 against 329.2 ms).
 template <int WR, int WC, int BI, int BJ>
 struct DL2 {
   static constexpr int NW = WR * WC, NTH = NW * 64, TM = 16 * BI * WR, TN = 16 * BJ * WC, BK = 16;
@@ -500,42 +175,33 @@ struct DL2 {
   static_assert((PA + PB) % NTH == 0 && PA % 64 == 0, "stage pieces per thread");
 };
 
-// Wait until at most N of this thread's vector memory loads are outstanding,
-// then meet the workgroup at a barrier; the statement's memory clobber keeps
-// the compiler from moving LDS accesses or direct-to-LDS loads across it.
-// (Unlike __syncthreads, whose release fence waits for every outstanding
-// direct-to-LDS load, this leaves the newer stages' loads in flight.)
+// Wait until at most N of this thread's vector memory loads are outstanding and
+// its LDS reads are done, then meet the workgroup at a barrier; the statement's
+// memory clobber keeps the compiler from moving LDS accesses or direct-to-LDS
+// loads across it.  Every stage's barrier is this one: __syncthreads() may
+// leave direct-to-LDS loads outstanding (the compiler waits for them before the
+// wave's own reads only, and the barrier is what tells the other waves), and
+// where it does wait, it waits for the newer stages' loads too.
 template <int N>
-__device__ __forceinline__ void wait_vm_barrier();
-template <>
-__device__ __forceinline__ void wait_vm_barrier<0>() { asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); }
-template <>
-__device__ __forceinline__ void wait_vm_barrier<4>() { asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory"); }
-template <>
-__device__ __forceinline__ void wait_vm_barrier<8>() { asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory"); }
-
-// LDS stages of the 64 x 64 list kernel (the batched products): 4, or 2 under
-// the measurement override BTA_LIST_STAGES=2.  (The single-problem 64 x 64
-// kernel keeps two stages: four measured no better there, where two stages
-// leave room for more workgroups per CU: n=128, b=2048 199.2 against 199.8 ms,
-// autograd 61.9 against 61.7 ms, the wide arrowhead 288.2 against 286.2 ms.)
-static int list_stages() {
-  static const int ns = [] {
-    long long v = 0;
-    return (env_int("BTA_LIST_STAGES", 2, 4, &v) && v == 2) ? 2 : 4;
-  }();
-  return ns;
+__device__ __forceinline__ void wait_vm_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// L0: layout of every problem's first segment as at * 2 + bt when the launch
+// shares one (its k loop then has no layout branch), 4 when it does not.
 // NS: LDS stages of the k loop.  2: the next stage's loads overlap this
 // stage's products.  NS > 2: NS - 1 stages in flight, each iteration waiting
 // only for its own stage's loads (vector memory loads complete in order) --
 // for tiles whose per-stage products are too short to cover a load's latency.
-template <int WR, int WC, int BI, int BJ, int L0, int NS = 2>
+// U: operands that the 16-byte pieces do not suit (odd leading dimensions,
+// extents or bases): 4 bytes per lane.
+template <int WR, int WC, int BI, int BJ, int L0, int NS = 2, bool U = false>
 __device__ __forceinline__ void gemm_tile_dl2(const GProb& P, long long local, int tid, double* lds) {
   using C = DL2<WR, WC, BI, BJ>;
   static_assert(NS == 2 || (NS == 4 && C::PER_T == 4), "the deep pipeline's wait counts assume 4 pieces per thread");
   constexpr int TM = C::TM, TN = C::TN, BK = C::BK, PER = C::PER_T;
+  constexpr int LPS = U ? 4 * PER : PER;  // loads per thread and stage
+  constexpr bool POINTERS = !U && TM == 128;
   const int batch = (int)(local / P.tiles_per_batch);
   const int tile = (int)(local - (long long)batch * P.tiles_per_batch);
   const int b0 = batch / P.nb1, b1 = batch - b0 * P.nb1;
@@ -564,13 +230,14 @@ __device__ __forceinline__ void gemm_tile_dl2(const GProb& P, long long local, i
   const int nk0 = (ke0 - kb0 + BK - 1) / BK;
   const int total = nk0 + (ke1 - kb1 + BK - 1) / BK;
 
-  // per piece: source pointer at the segment's first stage, its advance per
-  // stage, the piece's k offset within a stage, and whether it is inside M / N
+  // 128 x 128 tiles: per piece, its source pointer at the segment's first stage
+  // (resolved once per segment), its advance per stage, its k offset within a
+  // stage, and whether it is inside M / N
   const double* src[PER];
   int64_t inc[PER];
   int kpos[PER];
   bool inb[PER];
-  int seg_klen = 0;
+  int seg_klen = 0, stage_in_seg = 0;
   auto setup = [&](int sidx) {
     const GSeg& g = P.seg[sidx];
     const int kb = sidx == 0 ? kb0 : kb1;
@@ -603,20 +270,33 @@ __device__ __forceinline__ void gemm_tile_dl2(const GProb& P, long long local, i
       }
     }
   };
-  int stage_in_seg = 0;
   auto issue = [&](int kk) {
-    if (kk == 0) { setup(0); stage_in_seg = 0; }
-    if (kk == nk0) { setup(1); stage_in_seg = 0; }
+    const bool first = kk < nk0;
     double* st = lds + (kk % NS) * C::STAGE;
-    const int krel = stage_in_seg * BK;
-    const bool full = krel + BK <= seg_klen;
+    if constexpr (POINTERS) {
+      if (kk == 0) { setup(0); stage_in_seg = 0; }
+      if (kk == nk0) { setup(1); stage_in_seg = 0; }
+      const int krel = stage_in_seg * BK;
+      const bool full = krel + BK <= seg_klen;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const bool ok = inb[j] && (full || krel + kpos[j] < seg_klen);
-      load_piece_lds(ok ? src[j] : g_zero_piece, st + (wave * PER + j) * 128);
-      src[j] += inc[j];
+      for (int j = 0; j < PER; ++j) {
+        const bool ok = inb[j] && (full || krel + kpos[j] < seg_klen);
+        load_piece_lds(ok ? src[j] : g_zero_piece, st + (wave * PER + j) * 128);
+        src[j] += inc[j];
+      }
+      ++stage_in_seg;
+    } else {  // each wave moves pieces of one operand
+      const GSeg& g = P.seg[first ? 0 : 1];
+      const int k = first ? kb0 + kk * BK : kb1 + (kk - nk0) * BK;
+      const int kext = (first ? ke0 : ke1) - k;
+      constexpr int WA = C::NW / 2;  // waves that move A
+      static_assert(C::PA == C::PB, "equal pieces per wave");
+      if (wave < WA)
+        stage_pieces<TM, LPS, U ? 4 : 16>(g.A + b0 * g.sA0 + b1 * g.sA1, g.lda, g.at, m0, mext, k, kext, st, wave, lane);
+      else
+        stage_pieces<TN, LPS, U ? 4 : 16>(g.B + b0 * g.sB0 + b1 * g.sB1, g.ldb, g.bt, n0, next, k, kext, st + C::SA,
+                                          wave - WA, lane);
     }
-    ++stage_in_seg;
   };
 
   AccT<BI, BJ> acc;
@@ -651,10 +331,10 @@ __device__ __forceinline__ void gemm_tile_dl2(const GProb& P, long long local, i
     constexpr int LC = decltype(lc)::value;
     for (int kk = k0; kk < k1; ++kk) {
       if constexpr (NS == 2) {
-        __syncthreads();
+        wait_vm_barrier<0>();
       } else {  // stages kk + 1 .. kk + NS - 2 may stay in flight
-        if (kk + 2 < total) wait_vm_barrier<2 * C::PER_T>();
-        else if (kk + 1 < total) wait_vm_barrier<C::PER_T>();
+        if (kk + 2 < total) wait_vm_barrier<2 * LPS>();
+        else if (kk + 1 < total) wait_vm_barrier<LPS>();
         else wait_vm_barrier<0>();
       }
       const bool first = kk < nk0;
@@ -730,50 +410,15 @@ __device__ __forceinline__ int find_prob(const GemmArgs& args, long long t) {
   return j;
 }
 
-__global__ __launch_bounds__(NT, 2) void gemm_kernel(GemmArgs args) {
-  __shared__ double As[64 * 66];
-  __shared__ double Bs[64 * 66];
-  const int j = find_prob(args, blockIdx.x);
-  gemm_tile_body<2, 2, 64>(args.p[j], blockIdx.x - args.p[j].tile_begin, threadIdx.x, As, Bs);
-}
-
-__global__ __launch_bounds__(NT, 1) void gemm128_kernel(GemmArgs args) {
-  __shared__ double As[128 * 34];
-  __shared__ double Bs[128 * 34];
-  const int j = find_prob(args, blockIdx.x);
-  gemm_tile_body<4, 4, 32>(args.p[j], blockIdx.x - args.p[j].tile_begin, threadIdx.x, As, Bs);
-}
-
+// 64 x 64 tiles: four workgroups a CU (128 registers a lane).  The lower
+// products too: against a body with a bounds test per piece, n=32, b=4096 factor
+// and selected inversion 321.8 -> 317.7 ms, n=64, b=1024, a=256 35.9 -> 34.7 ms.
 template <int L0>
-__global__ __launch_bounds__(NT, 2) void gemm_dl128_kernel(GemmArgs args) {
-  __shared__ __align__(16) double lds[2 * DLCfg<4, 4>::STAGE];
-  const long long t = xcd_tile(blockIdx.x, gridDim.x);
-  const int j = find_prob(args, t);
-  gemm_tile_dl<4, 4, L0>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
-}
-
-template <int L0>
-__global__ __launch_bounds__(NT, 4) void gemm_dl64_kernel(GemmArgs args) {
-  __shared__ __align__(16) double lds[2 * DLCfg<2, 2>::STAGE];
-  const long long t = xcd_tile(blockIdx.x, gridDim.x);
-  const int j = find_prob(args, t);
-  gemm_tile_dl<2, 2, L0>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
-}
-
-template <int L0>
-__global__ __launch_bounds__(256, 2) void gemm_l64_kernel(GemmArgs args) {
+__global__ __launch_bounds__(256, 4) void gemm_l64_kernel(GemmArgs args) {
   __shared__ __align__(16) double lds[2 * DL2<2, 2, 2, 2>::STAGE];
   const long long t = xcd_tile(blockIdx.x, gridDim.x);
   const int j = find_prob(args, t);
   gemm_tile_dl2<2, 2, 2, 2, L0>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
-}
-
-template <int L0>
-__global__ __launch_bounds__(512, 3) void gemm_l128x64_kernel(GemmArgs args) {
-  __shared__ __align__(16) double lds[2 * DL2<4, 2, 2, 2>::STAGE];
-  const long long t = xcd_tile(blockIdx.x, gridDim.x);
-  const int j = find_prob(args, t);
-  gemm_tile_dl2<4, 2, 2, 2, L0>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
 }
 
 // 128 x 128 tiles: four LDS stages, three in flight (one workgroup per CU:
@@ -794,6 +439,21 @@ __global__ __launch_bounds__(512, 2) void gemm_l128s2_kernel(GemmArgs args) {
   const int j = find_prob(args, t);
   gemm_tile_dl2<4, 2, 2, 4, L0>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
 }
+// The same tiles from operands at any alignment (odd b or a).
+template <int L0>
+__global__ __launch_bounds__(256, 4) void gemm_u64_kernel(GemmArgs args) {
+  __shared__ __align__(16) double lds[2 * DL2<2, 2, 2, 2>::STAGE];
+  const long long t = xcd_tile(blockIdx.x, gridDim.x);
+  const int j = find_prob(args, t);
+  gemm_tile_dl2<2, 2, 2, 2, L0, 2, true>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
+}
+template <int L0>
+__global__ __launch_bounds__(512, 1) void gemm_u128_kernel(GemmArgs args) {
+  __shared__ __align__(16) double lds[4 * DL2<4, 2, 2, 4>::STAGE];
+  const long long t = xcd_tile(blockIdx.x, gridDim.x);
+  const int j = find_prob(args, t);
+  gemm_tile_dl2<4, 2, 2, 4, L0, 4, true>(args.p[j], t - args.p[j].tile_begin, threadIdx.x, lds);
+}
 static int l128_stages() {
   static const int ns = [] {
     long long v = 0;
@@ -805,7 +465,7 @@ static int l128_stages() {
 // Whether the direct-to-LDS bodies can take a problem: 16-byte aligned
 // operands, even leading dimensions, strides and k extents (their loads move
 // pairs of doubles).
-__host__ __device__ inline bool dl_ok(const GProb& p) {
+bool dl_ok(const GProb& p) {
   auto al = [](const double* q) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   for (int s = 0; s < p.nseg; ++s) {
     const GSeg& g = p.seg[s];
@@ -829,30 +489,28 @@ __device__ __forceinline__ int find_prob_list(const long long* tile_begin, int n
   return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// 64 x 64 tiles: the lean direct-to-LDS body where the problem allows it
-// (a workgroup-uniform test), with four LDS stages (three in flight: the
-// batched products have short k loops whose loads a single stage of products
-// cannot cover), the register-staged body otherwise.
-constexpr int LIST64_LDS = 2 * 64 * 66 > 4 * DL2<2, 2, 2, 2>::STAGE ? 2 * 64 * 66 : 4 * DL2<2, 2, 2, 2>::STAGE;
-template <int NS>
-__global__ __launch_bounds__(NT, 2) void gemm_list_kernel(const GProb* probs, const long long* tile_begin, int nprob) {
-  __shared__ __align__(16) double lds[LIST64_LDS];
+// 64 x 64 tiles: the lean direct-to-LDS body with two LDS stages and four
+// workgroups a CU.  The batched products have short k loops (K <= 390), so the
+// latency of a stage's loads is covered by the other workgroups' products
+// (64 matrices, n 16..96, b 128..384, factor and selected inversion: 38.0 ms
+// with four stages and two workgroups a CU, 35.3 ms now).  U: a problem of the
+// list needs the 4-byte loads; an instance of its own, as a test per workgroup
+// with both bodies in one kernel cost that workload 4%.
+template <bool U>
+__global__ __launch_bounds__(NT, 4) void gemm_list_kernel(const GProb* probs, const long long* tile_begin, int nprob) {
+  __shared__ __align__(16) double lds[2 * DL2<2, 2, 2, 2>::STAGE];
   const int j = find_prob_list(tile_begin, nprob, blockIdx.x);
   const GProb& P = probs[j];  // read in place: a private copy would live in scratch
-  const long long local = blockIdx.x - tile_begin[j];
-  if (dl_ok(P)) gemm_tile_dl2<2, 2, 2, 2, 4, NS>(P, local, threadIdx.x, lds);
-  else gemm_tile_body<2, 2, 64>(P, local, threadIdx.x, lds, lds + 64 * 66);
+  gemm_tile_dl2<2, 2, 2, 2, 4, 2, U>(P, blockIdx.x - tile_begin[j], threadIdx.x, lds);
 }
 
-// 128 x 128 tiles, likewise (the first direct-to-LDS body: 256 threads).
-constexpr int LIST128_LDS = 2 * 128 * 34 > 2 * DLCfg<4, 4>::STAGE ? 2 * 128 * 34 : 2 * DLCfg<4, 4>::STAGE;
-__global__ __launch_bounds__(NT, 1) void gemm128_list_kernel(const GProb* probs, const long long* tile_begin, int nprob) {
-  __shared__ __align__(16) double lds[LIST128_LDS];
+// 128 x 128 tiles, likewise (gemm_l128_kernel's shape).
+template <bool U>
+__global__ __launch_bounds__(512, 1) void gemm128_list_kernel(const GProb* probs, const long long* tile_begin, int nprob) {
+  __shared__ __align__(16) double lds[4 * DL2<4, 2, 2, 4>::STAGE];
   const int j = find_prob_list(tile_begin, nprob, blockIdx.x);
   const GProb& P = probs[j];  // read in place: a private copy would live in scratch
-  const long long local = blockIdx.x - tile_begin[j];
-  if (dl_ok(P)) gemm_tile_dl<4, 4, 4>(P, local, threadIdx.x, lds);
-  else gemm_tile_body<4, 4, 32>(P, local, threadIdx.x, lds, lds + 128 * 34);
+  gemm_tile_dl2<4, 2, 2, 4, 4, 4, U>(P, blockIdx.x - tile_begin[j], threadIdx.x, lds);
 }
 
 // Skinny products: at most SK_M rows of C, every segment with plain k ranges
@@ -951,14 +609,11 @@ hipError_t gemm_skinny_list_launch(const GProb* d_probs, const long long* d_tile
 }
 
 hipError_t gemm_list_launch(const GProb* d_probs, const long long* d_tile_begin, int nprob, long long ntiles, int big,
-                            hipStream_t stream) {
+                            bool pairs, hipStream_t stream) {
   if (ntiles <= 0) return hipSuccess;
-  if (big)
-    hipLaunchKernelGGL(gemm128_list_kernel, dim3((unsigned)ntiles), dim3(NT), 0, stream, d_probs, d_tile_begin, nprob);
-  else if (list_stages() == 2)
-    hipLaunchKernelGGL(gemm_list_kernel<2>, dim3((unsigned)ntiles), dim3(NT), 0, stream, d_probs, d_tile_begin, nprob);
-  else
-    hipLaunchKernelGGL(gemm_list_kernel<4>, dim3((unsigned)ntiles), dim3(NT), 0, stream, d_probs, d_tile_begin, nprob);
+  auto kernel = big ? (pairs ? gemm128_list_kernel<false> : gemm128_list_kernel<true>)
+                    : (pairs ? gemm_list_kernel<false> : gemm_list_kernel<true>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(big ? 512 : 256), 0, stream, d_probs, d_tile_begin, nprob);
   return hipGetLastError();
 }
 
@@ -1044,11 +699,8 @@ static long long plan_tiles(GemmArgs& args, GProb* probs, int nprob, int TM, int
   return total;
 }
 
-// Operands the direct-to-LDS body can move in 16-byte pieces.
-
-// 0: choose per launch; 1: register-staged kernels only; 2: direct-to-LDS
-// kernels wherever the operands allow; 3 / 4: first direct-to-LDS body with 64
-// / 128 tiles; 5 / 6 / 7: lean body with 64 x 64 / 128 x 64 / 128 x 128 tiles
+// 0: choose per launch; 1: the 4-byte loads only; 2: the 16-byte loads
+// wherever the operands allow; 3, 5: 64 x 64 tiles; 4, 6, 7: 128 x 128 tiles
 // (tests run every path through this).
 static int g_gemm_mode = 0;
 
@@ -1088,26 +740,23 @@ hipError_t gemm_launch(GProb* probs, int nprob, hipStream_t stream) {
   }
   bool dl = g_gemm_mode != 1;
   for (int i = 0; i < nprob; ++i) dl = dl && dl_ok(probs[i]);
-  GemmArgs big{}, small{}, mid{};
+  GemmArgs big{}, small{};
   const long long t128 = plan_tiles(big, probs, nprob, 128, 128);
   const long long t64 = plan_tiles(small, probs, nprob, 64, 64);
-  const long long t12864 = plan_tiles(mid, probs, nprob, 128, 64);
   if (t64 == 0) return hipSuccess;
-  if (dl) {
+  {
     int kind = g_gemm_mode >= 3 ? g_gemm_mode : 0;
-    if (kind == 0) {
+    if (!dl || kind == 0) {
       // 128 x 128 tiles (the most efficient per flop) when they fill the CUs
       // in whole rounds (at least 3/4 of the last round) and are mostly full
       // (ragged tiles cost nearly a whole tile of loads); otherwise 64 x 64
-      // tiles, with the first direct-to-LDS body for lower-triangle stores
-      // (fewer, unevenly sized tiles).
+      // tiles.
       const double cus = std::max(1, device_cu_count());
       const double rounds = std::ceil((double)t128 / cus);
       const bool fill = (double)t128 >= 0.75 * rounds * cus;
       const bool full = tile_weight(big, 128, 128) >= 0.85 * (double)t128;
-      bool lower_only = true;
-      for (int i = 0; i < nprob; ++i) lower_only = lower_only && probs[i].lower_tiles;
-      kind = (fill && full) ? 7 : (lower_only ? 3 : 5);
+      kind = (fill && full) ? 7 : 5;
+      if (!dl) kind = kind == 7 ? 9 : 8;
     }
     // the first segment's layout when every problem of the launch shares it
     int L0 = small.p[0].seg[0].at * 2 + small.p[0].seg[0].bt;
@@ -1123,31 +772,18 @@ hipError_t gemm_launch(GProb* probs, int nprob, hipStream_t stream) {
   }
     timing_mark(KT_GEMM, true, stream);
     switch (kind) {
-      case 3: BTA_LAUNCH_L0(gemm_dl64_kernel, t64, NT, small); break;
-      case 4: BTA_LAUNCH_L0(gemm_dl128_kernel, t128, NT, big); break;
-      case 5: BTA_LAUNCH_L0(gemm_l64_kernel, t64, 256, small); break;
-      case 7:
+      case 3: case 5: BTA_LAUNCH_L0(gemm_l64_kernel, t64, 256, small); break;
+      default:  // 4, 6, 7
         if (l128_stages() == 2) BTA_LAUNCH_L0(gemm_l128s2_kernel, t128, 512, big)
         else BTA_LAUNCH_L0(gemm_l128_kernel, t128, 512, big)
         break;
-      default: BTA_LAUNCH_L0(gemm_l128x64_kernel, t12864, 512, mid); break;
+      case 8: BTA_LAUNCH_L0(gemm_u64_kernel, t64, 256, small); break;
+      case 9: BTA_LAUNCH_L0(gemm_u128_kernel, t128, 512, big); break;
     }
 #undef BTA_LAUNCH_L0
     timing_mark(KT_GEMM, false, stream);
     return hipGetLastError();
   }
-  // 128 x 128 tiles when they alone give at least ~one tile per CU and every
-  // problem is at least 128 on both sides; 64 x 64 tiles otherwise.
-  bool use_big = t128 >= 200;
-  for (int i = 0; i < big.nprob; ++i)
-    if (big.p[i].M < 128 && big.p[i].N < 128) use_big = false;
-  timing_mark(KT_GEMM, true, stream);
-  if (use_big)
-    hipLaunchKernelGGL(gemm128_kernel, dim3((unsigned)t128), dim3(NT), 0, stream, big);
-  else
-    hipLaunchKernelGGL(gemm_kernel, dim3((unsigned)t64), dim3(NT), 0, stream, small);
-  timing_mark(KT_GEMM, false, stream);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- split-k
@@ -1461,6 +1097,7 @@ BTA_TESTING_API int bta_internal_gemm_list(int M, int N, int K, const double* A,
   std::vector<bta::GProb> ps(nprob);
   std::vector<long long> begin(nprob);
   long long tiles = 0;
+  bool pairs = true;
   for (int q = 0; q < nprob; ++q) {
     bta::GProb& p = ps[q];
     p = bta::GProb{};
@@ -1472,6 +1109,7 @@ BTA_TESTING_API int bta_internal_gemm_list(int M, int N, int K, const double* A,
     p.alpha = alpha; p.beta = beta; p.store = store; p.lower_tiles = lower_tiles;
     begin[q] = tiles;
     tiles += bta::gemm_prob_tiles(p, big ? 128 : 64);
+    pairs = pairs && bta::dl_ok(p);
   }
   char* d = static_cast<char*>(dlist);
   const size_t off = ((sizeof(bta::GProb) * nprob + 255) / 256) * 256;
@@ -1479,7 +1117,7 @@ BTA_TESTING_API int bta_internal_gemm_list(int M, int N, int K, const double* A,
   if (e == hipSuccess) e = hipMemcpyAsync(d + off, begin.data(), sizeof(long long) * nprob, hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
     e = bta::gemm_list_launch(reinterpret_cast<const bta::GProb*>(d), reinterpret_cast<const long long*>(d + off), nprob,
-                              tiles, big, s);
+                              tiles, big, pairs, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host copies are read before returning
   return (int)e;
 }

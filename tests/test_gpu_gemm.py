@@ -104,6 +104,40 @@ def test_gemm_kernels_match_reference(lib, case, mode):
     assert err < 1e-12
 
 
+# edges of the 64 and 128 tiles and of the 16-deep k stages, the smallest and a many-tile product
+ODD_SIZES = [(1, 1, 1), (63, 65, 15), (64, 64, 17), (65, 129, 33), (127, 127, 127), (129, 191, 257), (1151, 1793, 131)]
+
+
+@pytest.mark.parametrize("at,bt", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", ODD_SIZES)
+def test_gemm_operands_off_16_bytes(lib, M, N, K, at, bt):
+    """Odd leading dimensions and bases 8 bytes off a 16-byte line (the 4-byte
+    loads, 64 x 64 and, for the last size, 128 x 128 tiles), the cells around
+    the operands NaN: every element within the rounding bound of its own dot
+    product, K + 2 roundings of at most 2^-53 each."""
+    import torch
+
+    say(f"case gemm off 16 bytes M={M} N={N} K={K} at={at} bt={bt}")
+    rng = np.random.default_rng(M * 7919 + N * 31 + K + 2 * at + bt)
+    A, B, prod = _operands(rng, M, N, K, at, bt, TRI_NONE)
+    bound = (K + 2) * 2.0 ** -53 * 2.0 * (np.abs(A.T if at else A) @ np.abs(B.T if bt else B).T)
+
+    def odd(x):  # rows of an odd length, one element past a 16-byte line
+        ld = x.shape[1] + 1 + x.shape[1] % 2
+        flat = torch.full((x.shape[0] * ld + 2,), float("nan"), dtype=torch.float64, device="cuda")
+        flat[1:1 + x.shape[0] * ld].view(x.shape[0], ld)[:, :x.shape[1]] = torch.tensor(x)
+        return flat, flat.data_ptr() + 8, ld
+
+    fA, pA, lda = odd(A)
+    fB, pB, ldb = odd(B)
+    C = torch.zeros(M, N, dtype=torch.float64, device="cuda")
+    rc = lib.bta_internal_gemm(M, N, K, pA, lda, at, pB, ldb, bt, TRI_NONE, None, C.data_ptr(), N, 1.0, 0.0, ST_FULL, 0,
+                               torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0
+    assert (np.abs(C.cpu().numpy() - prod) <= bound).all()
+
+
 SPLIT_CASES = [
     # M, N, K, at, bt, store, lower_tiles, beta: the sweep's b x b product and its lower X_ii product
     (512, 512, 512, 0, 1, ST_FULL, 0, 0.0),
