@@ -5,14 +5,10 @@
 // The solve is memory bound (O(n b^2) reads of L per sweep) and sequential in
 // the block index.  The diagonal blocks are inverted up front in batched MFMA
 // launches (W_i = L_ii^{-1}, the same inverse-factor form as the selected
-// inversion), so that every step of both sweeps is a pair of dense
-// matrix-vector products spread over many workgroups:
-//   forward   t = y_i - L_{i,i-1} z_{i-1},               z_i = W_i t
-//   backward  t = z_i - L_{i+1,i}^T x_{i+1} - L_{n,i}^T x_n,  x_i = W_i^T t
-// with L_{i+1,i}^T and W_i^T transposed once into the workspace, so that every
-// product reads its matrix by rows (lanes along the row, coalesced), and the
-// arrow terms, which do not depend on the chain, computed for all blocks at
-// once.  Every sum runs in a fixed order (deterministic).
+// inversion), so that every step of both sweeps is a pair of dense products,
+// and each sweep is one persistent launch whose tasks (16 rows of a product)
+// hand their rows on without leaving the chip.  Every sum runs in a fixed order
+// (deterministic).
 #include <algorithm>
 
 #include "bta_device.hpp"
@@ -309,70 +305,385 @@ static hipError_t transpose_launch(const double* src, int64_t lds, int64_t ss, d
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void solve_gather_kernel(const double* rhs, int64_t nrhs, int64_t N, double* vec) {
-  const int64_t j = blockIdx.y;
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < N; r += (int64_t)gridDim.x * 256) vec[j * N + r] = rhs[r * nrhs + j];
-}
-__global__ __launch_bounds__(256) void solve_scatter_kernel(double* rhs, int64_t nrhs, int64_t N, const double* vec) {
-  const int64_t j = blockIdx.y;
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < N; r += (int64_t)gridDim.x * 256) rhs[r * nrhs + j] = vec[j * N + r];
+// ---------------------------------------------------------------- the chain of blocks
+// Right-hand sides travel in groups of NR: NR = 1 (vector FMAs) for at most
+// SOLVE_SINGLE of them, else 16 (one MFMA column block).  Element e of right-hand
+// side j is at ((j / NR) N + e) NR + j % NR, so a group is one array of rows.
+constexpr int64_t SOLVE_SINGLE = 4;
+constexpr int SOLVE_ROWS = 16;  // rows of a block's vector per task
+static int solve_group(int64_t nrhs) { return nrhs <= SOLVE_SINGLE ? 1 : 16; }
+__host__ __device__ inline int64_t rhs_at(int64_t j, int64_t e, int64_t N, int NR) { return (j / NR * N + e) * NR + j % NR; }
+
+// A vector element that no task has written yet (one NaN; a result with the
+// same bits is stored as its neighbour).
+constexpr unsigned long long SOLVE_PENDING = 0x7ff8b17ab17ab17aULL;
+
+// One sweep over blocks [i0, i1) as one launch: per block two phases,
+//   forward   t_i = y_i - L_{i,i-1} z_{i-1},    z_i = W_i t_i
+//   backward  t_i = y_i - L_{i+1,i}^T x_{i+1},  x_i = W_i^T t_i
+// each cut into tasks of SOLVE_ROWS rows of one group.  Tasks are taken from an
+// atomic counter in phase order, so a task only waits for tasks of smaller
+// tickets, which running workgroups own: no wait depends on how many workgroups
+// are resident.  A task's matrix elements do not depend on the chain and are
+// loaded before its wait; the transposed products read the matrix as it lies,
+// SOLVE_ROWS columns (a cache line) per task.
+struct ChainArgs {
+  const double* LB; const double* W;  // W of block i0 on
+  const double* y; double* t; double* z;  // phase 0 input, phase 0 and 1 outputs (groups of N, N, N rows)
+  int* flags;                         // NR = 16: [block][phase][group][task]
+  int* ctl;                           // ticket counter (64 bits), abort flag at ctl[2]
+  int64_t n, b, N, i0, i1;
+  int S, NG;                          // tasks per phase and group, groups
+  long long ntasks;
+};
+
+struct ChainTask {
+  int64_t i, r0, k0, k1;  // block, first row, k range
+  const double* M;        // matrix (nullptr: empty k range)
+  int64_t x, out;         // element offsets of x's and the output's block
+  const double* xb; const double* base; double* ob;
+  int s, g, ph;
+};
+
+template <bool BWD>
+__device__ __forceinline__ ChainTask chain_task(const ChainArgs& p, long long t) {
+  ChainTask k;
+  const long long per = (long long)p.S * p.NG, q = t / per;
+  const int rem = (int)(t - q * per);
+  k.s = rem / p.NG;
+  k.g = rem - k.s * p.NG;
+  k.ph = (int)(q & 1);
+  k.i = BWD ? p.i1 - 1 - (q >> 1) : p.i0 + (q >> 1);
+  k.r0 = (int64_t)SOLVE_ROWS * k.s;
+  const int64_t bb = p.b * p.b;
+  k.out = k.i * p.b;
+  if (k.ph == 0) {
+    const bool has = BWD ? k.i < p.n - 1 : k.i > 0;
+    k.M = has ? p.LB + (BWD ? k.i : k.i - 1) * bb : nullptr;
+    k.x = (BWD ? k.i + 1 : k.i - 1) * p.b;
+    k.k0 = 0;
+    k.k1 = has ? p.b : 0;
+    k.xb = p.z;
+    k.ob = p.t;
+    k.base = p.y;
+  } else {
+    k.M = p.W + (k.i - p.i0) * bb;
+    k.x = k.out;
+    k.k0 = BWD ? k.r0 : 0;
+    k.k1 = BWD ? p.b : std::min<int64_t>(p.b, k.r0 + SOLVE_ROWS);
+    k.xb = p.t;
+    k.ob = p.z;
+    k.base = nullptr;
+  }
+  return k;
 }
 
-// t[j][r] = vec[j][n*b + r] - sum_i ptip[j][i][r], the blocks summed in order.
-__global__ __launch_bounds__(256) void solve_tip_rhs_kernel(const double* vec, int64_t N, int64_t nb, const double* ptip,
-                                                            int64_t n, int64_t a, double* t) {
-  const int64_t j = blockIdx.y;
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < a; r += (int64_t)gridDim.x * 256) {
-    double acc = 0.0;
-    for (int64_t i = 0; i < n; ++i) acc += ptip[(j * n + i) * a + r];
-    t[j * a + r] = vec[j * N + nb + r] - acc;
+__device__ __forceinline__ long long chain_ticket(const ChainArgs& p, long long* sh, int tid) {
+  __syncthreads();  // the last task's reads of *sh and of the shared arrays
+  if (tid == 0) *sh = (long long)atomicAdd((unsigned long long*)p.ctl, 1ULL);
+  __syncthreads();
+  const long long t = *sh;
+  const int lo = __builtin_amdgcn_readfirstlane((int)t), hi = __builtin_amdgcn_readfirstlane((int)(t >> 32));
+  return ((long long)hi << 32) | (unsigned)lo;
+}
+
+constexpr long long CHAIN_SPIN = 1LL << 22;  // polls before a wait gives up (its outputs are then NaN)
+
+__device__ __forceinline__ bool chain_aborted(const ChainArgs& p) {
+  return __hip_atomic_load(p.ctl + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// One right-hand side per group.  The vectors carry their own readiness: every
+// element starts as SOLVE_PENDING, and a reader polls the elements it needs.
+// That leaves one store and one load of latency between phases, where a flag
+// behind the stores would add the wait for them and its own round trip.
+template <bool BWD>
+__global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
+  constexpr int KC = 1024;
+  __shared__ double xs[KC];
+  __shared__ double red[8 * SOLVE_ROWS];
+  __shared__ long long ticket;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (;;) {
+    const long long tk = chain_ticket(p, &ticket, tid);
+    if (tk >= p.ntasks) break;
+    const ChainTask q = chain_task<BWD>(p, tk);
+    const double* x = q.xb + q.g * p.N + q.x;
+    // forward: rows 2w, 2w + 1 of the task, lanes along k; backward: column
+    // tid % 16, rows tid / 16 + 32 j
+    const int64_t ra = std::min<int64_t>(q.r0 + 2 * w, p.b - 1), rb = std::min<int64_t>(q.r0 + 2 * w + 1, p.b - 1);
+    const int64_t cc = std::min<int64_t>(q.r0 + (tid & 15), p.b - 1);
+    const int rg = tid >> 4;
+    double m[32], s0 = 0.0, s1 = 0.0;
+    for (int64_t kc = q.k0; kc < q.k1; kc += KC) {
+      const int64_t left = q.k1 - kc;
+      if constexpr (!BWD) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const int64_t k = kc + std::min<int64_t>(64 * c + lane, left - 1);
+          m[c] = q.M[ra * p.b + k];
+          m[16 + c] = q.M[rb * p.b + k];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 32; ++j) m[j] = q.M[(kc + std::min<int64_t>(rg + 32 * j, left - 1)) * p.b + cc];
+      }
+      if (kc > q.k0) __syncthreads();  // xs is read
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int e = tid + 512 * h;
+        double v = 0.0;
+        if (e < left) {
+          v = ld_dev(x + kc + e);
+          long long polls = 0;
+          while (__builtin_bit_cast(unsigned long long, v) == SOLVE_PENDING) {
+            if (++polls > CHAIN_SPIN || ((polls & 63) == 0 && chain_aborted(p))) {
+              __hip_atomic_store(p.ctl + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            v = ld_dev(x + kc + e);
+          }
+        }
+        xs[e] = v;
+      }
+      __syncthreads();
+      // elements past the range were read from its last one: they count as zero
+      if constexpr (!BWD) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const bool in = 64 * c + lane < left;
+          s0 = __builtin_fma(in ? m[c] : 0.0, xs[64 * c + lane], s0);
+          s1 = __builtin_fma(in ? m[16 + c] : 0.0, xs[64 * c + lane], s1);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 32; ++j) s0 = __builtin_fma(rg + 32 * j < left ? m[j] : 0.0, xs[rg + 32 * j], s0);
+      }
+    }
+    if constexpr (!BWD) {
+      s0 = wave_sum(s0);
+      s1 = wave_sum(s1);
+      if (lane < 2) red[2 * w + lane] = lane ? s1 : s0;
+    } else {
+      s0 += __shfl_xor(s0, 16, 64);
+      s0 += __shfl_xor(s0, 32, 64);
+      if (lane < 16) red[16 * w + lane] = s0;
+    }
+    __syncthreads();
+    if (tid < SOLVE_ROWS && q.r0 + tid < p.b) {
+      double v = red[tid];
+      if constexpr (BWD) {
+#pragma unroll
+        for (int u = 1; u < 8; ++u) v += red[16 * u + tid];
+      }
+      const int64_t e = q.g * p.N + q.out + q.r0 + tid;
+      if (q.base) v = q.base[e] - v;
+      if (__builtin_bit_cast(unsigned long long, v) == SOLVE_PENDING)
+        v = __builtin_bit_cast(double, SOLVE_PENDING ^ 1ULL);
+      st_dev(q.ob + e, v);
+    }
   }
 }
 
-// vec[j][i*b + c] -= sum_{r<a} L_{n,i}[r][c] x_n[r] for every block i < n
+// Sixteen right-hand sides per group on MFMA: a task's 16 x 16 output is
+// accumulated by eight waves, each a share of the k range, and summed in wave
+// order.  Readiness is a flag per task: a poll of every element, as for one
+// right-hand side, would repeat 128 bytes per row.
+template <bool BWD>
+__global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
+  constexpr int KC = 512, Q = KC / 128;  // k per chunk, groups of 16 k per wave
+  __shared__ double red[8 * 256];
+  __shared__ long long ticket;
+  __shared__ int good;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mn = lane & 15, g4 = 4 * (lane >> 4);
+  for (;;) {
+    const long long tk = chain_ticket(p, &ticket, tid);
+    if (tk >= p.ntasks) break;
+    const ChainTask q = chain_task<BWD>(p, tk);
+    const double* x = q.xb + (q.g * p.N + q.x) * 16;
+    const int64_t rm = std::min<int64_t>(q.r0 + mn, p.b - 1);
+    const double* M = q.M + (BWD ? rm : rm * p.b);
+    struct __attribute__((packed, aligned(8))) Row4 { d4 v; };  // four k of a row, any 8-byte alignment
+    bool ok = true;
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t kc = q.k0; kc < q.k1; kc += KC) {
+      double a[Q][4], v[Q][4];
+#pragma unroll
+      for (int u = 0; u < Q; ++u) {
+        const int64_t k = kc + 16 * (w + 8 * u);
+        if (!BWD && k + 16 <= q.k1) {
+          const d4 r = reinterpret_cast<const Row4*>(M + k + g4)->v;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) a[u][j] = r[j];
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) a[u][j] = M[std::min<int64_t>(k + g4 + j, q.k1 - 1) * (BWD ? p.b : 1)];
+        }
+      }
+      if (kc == q.k0) {
+        // the slices of the previous phase that this task reads
+        const int64_t ib = q.ph ? q.i : BWD ? q.i + 1 : q.i - 1;
+        const int* f = p.flags + ((ib * 2 + (1 - q.ph)) * p.NG + q.g) * p.S;
+        const int f0 = (BWD && q.ph) ? q.s : 0, f1 = (!BWD && q.ph) ? q.s + 1 : p.S;
+        if (w == 0) {
+          long long polls = 0;
+          for (int e = f0 + lane; e < f1; e += 64)
+            while (!flag_set(f + e)) {
+              if (++polls > CHAIN_SPIN || ((polls & 63) == 0 && chain_aborted(p))) {
+                __hip_atomic_store(p.ctl + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+              }
+              __builtin_amdgcn_s_sleep(1);
+            }
+          if (tid == 0) good = chain_aborted(p) ? 0 : 1;
+        }
+        __syncthreads();
+        ok = good != 0;
+      }
+#pragma unroll
+      for (int u = 0; u < Q; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int64_t k = kc + 16 * (w + 8 * u) + g4 + j;
+          v[u][j] = ld_dev(x + std::min<int64_t>(k, q.k1 - 1) * 16 + mn);
+        }
+#pragma unroll
+      for (int u = 0; u < Q; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool in = kc + 16 * (w + 8 * u) + g4 + j < q.k1;
+          acc = mfma16(in ? a[u][j] : 0.0, in ? v[u][j] : 0.0, acc);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[w * 256 + acc_row(lane, j) * 16 + acc_col(lane)] = acc[j];
+    __syncthreads();
+    if (tid < 256 && q.r0 + (tid >> 4) < p.b) {
+      double v = red[tid];
+#pragma unroll
+      for (int u = 1; u < 8; ++u) v += red[256 * u + tid];
+      const int64_t e = (q.g * p.N + q.out + q.r0) * 16 + tid;
+      if (q.base) v = q.base[e] - v;
+      st_dev(q.ob + e, ok ? v : __builtin_nan(""));
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    // every wave's stores are complete at device scope: the flag needs no
+    // release of its own (which would write the L2 back), nor its readers an
+    // acquire (which would invalidate it), as x is read at device scope too
+    if (tid == 0)
+      __hip_atomic_store(p.flags + ((q.i * 2 + q.ph) * p.NG + q.g) * p.S + q.s, 1, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// The right-hand sides into groups (padded with zero columns), the vectors of
+// both sweeps to pending, and the flags and ticket counters to zero.
+__global__ __launch_bounds__(256) void solve_gather_kernel(const double* rhs, int64_t nrhs, int64_t N, int NR, int64_t NG,
+                                                           double* y, unsigned long long* pend, int64_t npend, int* zero,
+                                                           int64_t nzero) {
+  const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  for (int64_t e = t0; e < NG * N * NR; e += step) {
+    const int64_t row = e / NR, j = row / N * NR + e % NR;
+    y[e] = j < nrhs ? rhs[row % N * nrhs + j] : 0.0;
+  }
+  for (int64_t e = t0; e < npend; e += step) pend[e] = SOLVE_PENDING;
+  for (int64_t e = t0; e < nzero; e += step) zero[e] = 0;
+}
+__global__ __launch_bounds__(256) void solve_scatter_kernel(double* rhs, int64_t nrhs, int64_t N, int64_t nb, int NR,
+                                                            const double* x, const double* xn) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < N * nrhs; e += (int64_t)gridDim.x * 256) {
+    const int64_t r = e / nrhs, j = e - r * nrhs;
+    rhs[e] = r < nb ? x[rhs_at(j, r, N, NR)] : xn[j * (N - nb) + r - nb];
+  }
+}
+
+// ptip(j, i, r) = sum_k L_{n,i}[r][k] z_i(j)[k] for one group of 16 per
+// workgroup: thread (k residue, right-hand side), residues summed in order.
+__global__ __launch_bounds__(256) void solve_tip16_kernel(const double* LR, int64_t b, int64_t a, int64_t n, int64_t N,
+                                                          const double* z, double* ptip) {
+  __shared__ double red[256];
+  const int64_t r = blockIdx.x, i = blockIdx.y, g = blockIdx.z;
+  const double* M = LR + (i * a + r) * b;
+  const double* zi = z + (g * N + i * b) * 16;
+  double s = 0.0;
+  for (int64_t k = threadIdx.x >> 4; k < b; k += 16) s = __builtin_fma(M[k], zi[k * 16 + (threadIdx.x & 15)], s);
+  red[threadIdx.x] = s;
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    for (int u = 1; u < 16; ++u) s += red[16 * u + threadIdx.x];
+    ptip[((g * n + i) * a + r) * 16 + threadIdx.x] = s;
+  }
+}
+
+// t[j][r] = y(j)[n*b + r] - sum_i ptip(j, i, r), the blocks summed in order.
+__global__ __launch_bounds__(256) void solve_tip_rhs_kernel(const double* y, int64_t N, int64_t nb, const double* ptip,
+                                                            int64_t n, int64_t a, int NR, double* t) {
+  const int64_t j = blockIdx.y;
+  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < a; r += (int64_t)gridDim.x * 256) {
+    double acc = 0.0;
+    for (int64_t i = 0; i < n; ++i) acc += ptip[rhs_at(j, i * a + r, n * a, NR)];
+    t[j * a + r] = y[rhs_at(j, nb + r, N, NR)] - acc;
+  }
+}
+
+// z(j)[i*b + c] -= sum_{r<a} L_{n,i}[r][c] x_n(j)[r] for every block i < n
 // (the arrow terms of the backward sweep: x_n is final before it starts).
 __global__ __launch_bounds__(256) void solve_arrow_terms_kernel(const double* LR, int64_t n, int64_t b, int64_t a,
-                                                                const double* xn, int64_t N, double* vec) {
-  const int64_t j = blockIdx.y;
-  const int64_t total = n * b;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-    const int64_t i = e / b, c = e - i * b;
+                                                                const double* xn, int64_t nrhs, int64_t N, int NR, double* z) {
+  const int64_t g = blockIdx.y;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n * b * NR; e += (int64_t)gridDim.x * 256) {
+    const int64_t row = e / NR, j = g * NR + e % NR, i = row / b, c = row - i * b;
+    if (j >= nrhs) continue;
     const double* M = LR + i * a * b + c;
-    const double* x = xn + j * N;
+    const double* x = xn + j * a;
     double acc = 0.0;
     for (int64_t r = 0; r < a; ++r) acc = __builtin_fma(M[r * b], x[r], acc);
-    vec[j * N + e] -= acc;
+    z[g * N * NR + e] -= acc;
   }
 }
 
 // Workspace layout of one solve.  C blocks per chunk of inverses: the whole
-// matrix when the inverses, their transposes and the transposed coupling
-// blocks fit in the budget (then each inverse is formed once for both
-// sweeps), else chunks that are formed again for the backward sweep.
+// matrix when its inverses fit in the budget beside the scratch that forms them
+// (C1 blocks at a time), else chunks; the backward sweep then forms all but the
+// last one again.
 struct SolvePlan {
-  int64_t C, nchunks;
-  size_t off_W, off_T1, off_LBt, off_WT, off_WTt, off_vec, off_t, off_t2, off_ptip, bytes;
+  int64_t C, C1, nchunks, NG, npend, nzero;
+  int NR, S;
+  size_t off_W, off_T1, off_WT, off_WTt, off_y, off_pend, off_zero, off_t, off_t2, off_xn, off_ptip, bytes;
 };
 
 static SolvePlan solve_plan(int64_t n, int64_t b, int64_t a, int64_t nrhs) {
   SolvePlan sp{};
-  const size_t per_block = 3 * 8 * (size_t)b * (size_t)b;
+  const size_t per_block = 8 * (size_t)b * (size_t)b;
   const size_t budget = size_t(2) << 30;
-  sp.C = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(budget / per_block)));
+  sp.C1 = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)((budget >> 2) / per_block)));
+  sp.C = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(budget / per_block) - sp.C1));
+  sp.C1 = std::min(sp.C1, sp.C);
   sp.nchunks = (n + sp.C - 1) / sp.C;
   const int64_t N = n * b + a;
+  sp.NR = solve_group(nrhs);
+  sp.NG = (nrhs + sp.NR - 1) / sp.NR;
+  sp.S = (int)((b + SOLVE_ROWS - 1) / SOLVE_ROWS);
+  const int64_t nv = sp.NG * N * sp.NR;
+  sp.npend = 4 * nv;  // t and the result of each sweep
+  // per sweep and chunk a ticket counter and an abort flag (4 ints), then the flags of both sweeps
+  sp.nzero = 8 * sp.nchunks + (sp.NR > 1 ? 4 * n * sp.NG * sp.S : 0);
   size_t off = 0;
   auto take = [&](size_t x) { size_t o = off; off += (std::max<size_t>(x, 8) + 255) & ~size_t(255); return o; };
-  const size_t cbb = 8 * (size_t)sp.C * (size_t)b * (size_t)b;
-  sp.off_W = take(cbb);
-  sp.off_T1 = take(cbb);
-  sp.off_LBt = take(cbb);
+  sp.off_W = take(per_block * (size_t)sp.C);
+  sp.off_T1 = take(per_block * (size_t)sp.C1);
   sp.off_WT = take(8 * (size_t)(a * a));
   sp.off_WTt = take(8 * (size_t)(a * a));
-  sp.off_vec = take(8 * (size_t)(N * nrhs));
-  sp.off_t = take(8 * (size_t)(std::max(b, a) * nrhs));
+  sp.off_y = take(8 * (size_t)nv);
+  sp.off_pend = take(8 * (size_t)sp.npend);
+  sp.off_zero = take(4 * (size_t)sp.nzero);
+  sp.off_t = take(8 * (size_t)(a * nrhs));
   sp.off_t2 = take(8 * (size_t)(a * nrhs));
-  sp.off_ptip = take(8 * (size_t)(n * a * nrhs));
+  sp.off_xn = take(8 * (size_t)(a * nrhs));
+  sp.off_ptip = take(8 * (size_t)(n * a * sp.NG * sp.NR));
   sp.bytes = off;
   return sp;
 }
@@ -383,61 +694,67 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
                         const double* LT, double* rhs, int64_t nrhs, void* work, hipStream_t stream) {
   const SolvePlan sp = solve_plan(n, b, a, nrhs);
   char* w = static_cast<char*>(work);
-  double* W = reinterpret_cast<double*>(w + sp.off_W);
-  double* T1 = reinterpret_cast<double*>(w + sp.off_T1);   // TRTRI scratch, then W_i^T
-  double* LBt = reinterpret_cast<double*>(w + sp.off_LBt);
-  double* WT = reinterpret_cast<double*>(w + sp.off_WT);
-  double* WTt = reinterpret_cast<double*>(w + sp.off_WTt);
-  double* vec = reinterpret_cast<double*>(w + sp.off_vec);
-  double* tb = reinterpret_cast<double*>(w + sp.off_t);
-  double* t2 = reinterpret_cast<double*>(w + sp.off_t2);
-  double* ptip = reinterpret_cast<double*>(w + sp.off_ptip);
-  const int64_t N = n * b + a, bb = b * b, ab = a * b;
+  auto at = [&](size_t off) { return reinterpret_cast<double*>(w + off); };
+  double *W = at(sp.off_W), *T1 = at(sp.off_T1), *WT = at(sp.off_WT), *WTt = at(sp.off_WTt), *y = at(sp.off_y);
+  double *tb = at(sp.off_t), *t2 = at(sp.off_t2), *xn = at(sp.off_xn), *ptip = at(sp.off_ptip);
+  const int64_t N = n * b + a, bb = b * b, ab = a * b, nv = sp.NG * N * sp.NR;
+  double *pt = at(sp.off_pend), *pz = pt + nv, *qt = pz + nv, *qx = qt + nv;
+  int* ctl = reinterpret_cast<int*>(w + sp.off_zero);
+  int* flags = ctl + 8 * sp.nchunks;
   const int nr = (int)nrhs;
-  const int64_t tstride = std::max(b, a);
   auto ok = [&]() { return hipGetLastError(); };
+  auto blocks = [](int64_t count) { return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (count + 255) / 256))); };
 
-  const unsigned gN = (unsigned)std::min<int64_t>(1024, (N + 255) / 256);
-  hipLaunchKernelGGL(solve_gather_kernel, dim3(gN, (unsigned)nrhs), dim3(256), 0, stream, rhs, nrhs, N, vec);
+  hipLaunchKernelGGL(solve_gather_kernel, blocks(sp.npend), dim3(256), 0, stream, rhs, nrhs, N, sp.NR, sp.NG, y,
+                     reinterpret_cast<unsigned long long*>(pt), sp.npend, ctl, sp.nzero);
   if (hipError_t e = ok()) return e;
 
   auto invert_chunk = [&](int64_t i0, int64_t cnt) -> hipError_t {
     BTA_TRY_E(fill_zero_launch(W, (size_t)(cnt * bb), stream));
-    return trtri_batched(LD + i0 * bb, b, bb, W, T1, b, bb, (int)b, (int)cnt, stream, 0, 0);
+    for (int64_t q = 0; q < cnt; q += sp.C1)
+      BTA_TRY_E(trtri_batched(LD + (i0 + q) * bb, b, bb, W + q * bb, T1, b, bb, (int)b, (int)std::min(sp.C1, cnt - q), stream,
+                              0, 0));
+    return hipSuccess;
+  };
+  // one sweep over a chunk: enough workgroups for two phases in flight (the
+  // second has its matrix elements loaded when the first ends), at most one a CU
+  auto chain = [&](bool bwd, int64_t c, const double* in, double* t, double* z) -> hipError_t {
+    ChainArgs p{};
+    p.LB = LB; p.W = W; p.y = in; p.t = t; p.z = z;
+    p.flags = flags + (bwd ? 2 * n * sp.NG * sp.S : 0);
+    p.ctl = ctl + 4 * (2 * c + (bwd ? 1 : 0));
+    p.n = n; p.b = b; p.N = N; p.i0 = c * sp.C; p.i1 = std::min(n, p.i0 + sp.C);
+    p.S = sp.S; p.NG = (int)sp.NG;
+    p.ntasks = 2 * (p.i1 - p.i0) * sp.NG * sp.S;
+    const long long grid = std::min<long long>(std::max(1, device_cu_count()), 2 * sp.NG * sp.S);
+    auto kernel = sp.NR == 1 ? (bwd ? solve_chain_kernel<true> : solve_chain_kernel<false>)
+                             : (bwd ? solve_chain16_kernel<true> : solve_chain16_kernel<false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(512), 0, stream, p);
+    return ok();
   };
 
-  // ---- forward: z_i = W_i (y_i - L_{i,i-1} z_{i-1})
   for (int64_t c = 0; c < sp.nchunks; ++c) {
-    const int64_t i0 = c * sp.C, cnt = std::min<int64_t>(sp.C, n - i0);
-    BTA_TRY_E(invert_chunk(i0, cnt));
-    for (int64_t i = i0; i < i0 + cnt; ++i) {
-      MvArgs cp{};
-      cp.M = i > 0 ? LB + (i - 1) * bb : nullptr; cp.ld = b;
-      cp.x = vec + (i - 1) * b; cp.sxy = N;
-      cp.base = vec + i * b; cp.sby = N;
-      cp.out = tb; cp.soy = tstride;
-      cp.rows = b; cp.K = i > 0 ? b : 0; cp.tri = 0; cp.sign = -1.0;
-      BTA_TRY_E(matvec_rows(cp, nr, 1, stream));
-      MvArgs ap{};
-      ap.M = W + (i - i0) * bb; ap.ld = b;
-      ap.x = tb; ap.sxy = tstride;
-      ap.out = vec + i * b; ap.soy = N;
-      ap.rows = b; ap.K = b; ap.tri = 1; ap.sign = 1.0;
-      BTA_TRY_E(matvec_rows(ap, nr, 1, stream));
-    }
+    BTA_TRY_E(invert_chunk(c * sp.C, std::min<int64_t>(sp.C, n - c * sp.C)));
+    BTA_TRY_E(chain(false, c, y, pt, pz));
   }
 
   // ---- the tip: z_n = W_T (y_n - sum_i L_{n,i} z_i), x_n = W_T^T z_n, then
   // the arrow terms of every block's backward right-hand side
   if (a > 0) {
-    MvArgs pp{};
-    pp.M = LR; pp.ld = b; pp.sMz = ab;
-    pp.x = vec; pp.sxy = N; pp.sxz = b;
-    pp.out = ptip; pp.soy = n * a; pp.soz = a;
-    pp.rows = a; pp.K = b; pp.tri = 0; pp.sign = 1.0;
-    BTA_TRY_E(matvec_rows(pp, nr, (int)n, stream));
-    hipLaunchKernelGGL(solve_tip_rhs_kernel, dim3((unsigned)((a + 255) / 256), (unsigned)nrhs), dim3(256), 0, stream, vec,
-                       N, n * b, ptip, n, a, t2);
+    if (sp.NR == 1) {
+      MvArgs pp{};
+      pp.M = LR; pp.ld = b; pp.sMz = ab;
+      pp.x = pz; pp.sxy = N; pp.sxz = b;
+      pp.out = ptip; pp.soy = n * a; pp.soz = a;
+      pp.rows = a; pp.K = b; pp.tri = 0; pp.sign = 1.0;
+      BTA_TRY_E(matvec_rows(pp, nr, (int)n, stream));
+    } else {
+      hipLaunchKernelGGL(solve_tip16_kernel, dim3((unsigned)a, (unsigned)n, (unsigned)sp.NG), dim3(256), 0, stream, LR, b, a,
+                         n, N, pz, ptip);
+      if (hipError_t e = ok()) return e;
+    }
+    hipLaunchKernelGGL(solve_tip_rhs_kernel, dim3((unsigned)((a + 255) / 256), (unsigned)nrhs), dim3(256), 0, stream, y, N,
+                       n * b, ptip, n, a, sp.NR, t2);
     if (hipError_t e = ok()) return e;
     BTA_TRY_E(fill_zero_launch(WT, (size_t)(a * a), stream));
     BTA_TRY_E(trtri_batched(LT, a, 0, WT, WTt, a, 0, (int)a, 1, stream, 0, 0));
@@ -445,45 +762,26 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
     MvArgs fz{};
     fz.M = WT; fz.ld = a;
     fz.x = t2; fz.sxy = a;
-    fz.out = tb; fz.soy = tstride;
+    fz.out = tb; fz.soy = a;
     fz.rows = a; fz.K = a; fz.tri = 1; fz.sign = 1.0;
     BTA_TRY_E(matvec_rows(fz, nr, 1, stream));
     MvArgs bx{};
     bx.M = WTt; bx.ld = a;
-    bx.x = tb; bx.sxy = tstride;
-    bx.out = vec + n * b; bx.soy = N;
+    bx.x = tb; bx.sxy = a;
+    bx.out = xn; bx.soy = a;
     bx.rows = a; bx.K = a; bx.tri = 2; bx.sign = 1.0;
     BTA_TRY_E(matvec_rows(bx, nr, 1, stream));
-    const unsigned g = (unsigned)std::min<int64_t>(4096, (n * b + 255) / 256);
-    hipLaunchKernelGGL(solve_arrow_terms_kernel, dim3(g, (unsigned)nrhs), dim3(256), 0, stream, LR, n, b, a, vec + n * b, N,
-                       vec);
+    dim3 g = blocks(n * b * sp.NR);
+    g.y = (unsigned)sp.NG;
+    hipLaunchKernelGGL(solve_arrow_terms_kernel, g, dim3(256), 0, stream, LR, n, b, a, xn, nrhs, N, sp.NR, pz);
     if (hipError_t e = ok()) return e;
   }
 
-  // ---- backward: x_i = W_i^T (z_i - L_{n,i}^T x_n - L_{i+1,i}^T x_{i+1})
   for (int64_t c = sp.nchunks - 1; c >= 0; --c) {
-    const int64_t i0 = c * sp.C, cnt = std::min<int64_t>(sp.C, n - i0);
-    if (sp.nchunks > 1) BTA_TRY_E(invert_chunk(i0, cnt));
-    BTA_TRY_E(transpose_launch(W, b, bb, T1, b, bb, b, b, (int)cnt, stream));
-    const int64_t nsub = std::min<int64_t>(cnt, (n - 1) - i0);
-    if (nsub > 0) BTA_TRY_E(transpose_launch(LB + i0 * bb, b, bb, LBt, b, bb, b, b, (int)nsub, stream));
-    for (int64_t i = i0 + cnt - 1; i >= i0; --i) {
-      MvArgs cp{};
-      cp.M = i < n - 1 ? LBt + (i - i0) * bb : nullptr; cp.ld = b;
-      cp.x = vec + (i + 1) * b; cp.sxy = N;
-      cp.base = vec + i * b; cp.sby = N;
-      cp.out = tb; cp.soy = tstride;
-      cp.rows = b; cp.K = i < n - 1 ? b : 0; cp.tri = 0; cp.sign = -1.0;
-      BTA_TRY_E(matvec_rows(cp, nr, 1, stream));
-      MvArgs ap{};
-      ap.M = T1 + (i - i0) * bb; ap.ld = b;
-      ap.x = tb; ap.sxy = tstride;
-      ap.out = vec + i * b; ap.soy = N;
-      ap.rows = b; ap.K = b; ap.tri = 2; ap.sign = 1.0;
-      BTA_TRY_E(matvec_rows(ap, nr, 1, stream));
-    }
+    if (c < sp.nchunks - 1) BTA_TRY_E(invert_chunk(c * sp.C, sp.C));
+    BTA_TRY_E(chain(true, c, pz, qt, qx));
   }
-  hipLaunchKernelGGL(solve_scatter_kernel, dim3(gN, (unsigned)nrhs), dim3(256), 0, stream, rhs, nrhs, N, vec);
+  hipLaunchKernelGGL(solve_scatter_kernel, blocks(N * nrhs), dim3(256), 0, stream, rhs, nrhs, N, n * b, sp.NR, qx, xn);
   return ok();
 }
 

@@ -182,6 +182,46 @@ def test_solve_and_logdet(torch_cuda, n, b, a, nrhs):
     assert abs(float(ld.item()) - ldo) <= TOL * abs(ldo)
 
 
+# edges of a task's 16 rows, of a wave's and a chunk's k range (512, 1024), one and
+# several groups of right-hand sides (up to 4 singly, then 16 at a time), wide tips
+@pytest.mark.parametrize("n,b,a,nrhs", [(1, 1, 0, 5), (3, 15, 1, 4), (4, 16, 0, 16), (3, 17, 3, 17), (3, 513, 2, 5),
+                                        (3, 530, 70, 33), (3, 1025, 2, 1), (2, 1040, 130, 4), (5, 128, 40, 64)])
+def test_solve_groups(torch_cuda, n, b, a, nrhs):
+    test_solve_and_logdet(torch_cuda, n, b, a, nrhs)
+
+
+@pytest.mark.parametrize("nrhs", [1, 6])
+def test_solve_chunks(torch_cuda, nrhs):
+    """More blocks than inverses fit in the workspace at once (14 of 4096: two
+    chunks, the first formed again for the backward sweep): x from y = L L^T x."""
+    from paper_2503_17528_amd import bta
+
+    torch, n, b, a = torch_cuda, 14, 4096, 3
+    say(f"case solve in chunks n={n} b={b} a={a} nrhs={nrhs}")
+    wl = synth.workload(n, b, a, "scaled")
+    L = [torch.zeros(z, dtype=torch.float64, device="cuda") for z in ((n, b, b), (n - 1, b, b), (n, a, b), (a, a))]
+    for i in range(n):
+        L[0][i] = synth.factor_block_torch(wl, 2, synth.KIND_DIAG, i, "cuda")
+        L[2][i] = synth.factor_block_torch(wl, 2, synth.KIND_ARROW, i, "cuda")
+        if i < n - 1:
+            L[1][i] = synth.factor_block_torch(wl, 2, synth.KIND_SUB, i, "cuda")
+    L[3].copy_(synth.factor_block_torch(wl, 2, synth.KIND_TIP, 0, "cuda"))
+    x = torch.randn(n * b + a, nrhs, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(4))
+    xb, xt = x[:n * b].view(n, b, nrhs), x[n * b:]
+    u = torch.zeros_like(xb)  # L^T x, then L u
+    for i in range(n):
+        u[i] = L[0][i].T @ xb[i] + L[2][i].T @ xt + (L[1][i].T @ xb[i + 1] if i < n - 1 else 0.0)
+    ut = L[3].T @ xt
+    y = torch.zeros_like(x)
+    for i in range(n):
+        y[i * b:(i + 1) * b] = L[0][i] @ u[i] + (L[1][i - 1] @ u[i - 1] if i else 0.0)
+    y[n * b:] = L[3] @ ut + sum(L[2][i] @ u[i] for i in range(n))
+    got = bta.solve(*L, y)
+    e = float((got - x).norm() / x.norm())
+    say(f"   solve rel err {e:.3e}")
+    assert e < TOL
+
+
 def test_abi_rejects_bad_workspace_on_device(torch_cuda):
     from paper_2503_17528_amd import bta
 
