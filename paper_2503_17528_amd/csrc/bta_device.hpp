@@ -437,6 +437,20 @@ __device__ __forceinline__ void mma16x16(d4& c, const double* A, int lda, const 
   c = mfma16(sgn * a23[1], b3, c);
 }
 
+// c -= A^T B for 16 x 16 blocks: A(m,k) at A[k*lda + m], B(k,n) at B[k*ldb + n].
+__device__ __forceinline__ void mma16x16_ta(d4& c, const double* A, int lda, const double* B, int ldb, int lane) {
+  const int mn = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = mfma16(-A[(4 * g + s) * lda + mn], B[(4 * g + s) * ldb + mn], c);
+}
+// One wave: X = Y^T for 16 x 16 blocks of row stride LDS_LD.
+__device__ __forceinline__ void blk_transpose(double* X, const double* Y, int lane) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = 4 * j + (lane >> 4), col = lane & 15;
+    X[row * LDS_LD + col] = Y[col * LDS_LD + row];
+  }
+}
 __device__ __forceinline__ void blk_load(d4& c, const double* X, int ld, int lane) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) c[j] = X[acc_row(lane, j) * ld + acc_col(lane)];
@@ -447,45 +461,71 @@ __device__ __forceinline__ void blk_store(const d4& c, double* X, int ld, int la
 }
 
 // Cholesky factor and inverse of the SPD tile S (64 x 64, LDS row stride
-// LDS_LD; only its lower triangle is read).  On return the lower triangle of S
+// LDS_LD; only its lower triangle is read, and the identity blocks that
+// chol_prepare has put above it).  On return the lower triangle of S
 // holds L (the values above it are stale: store it with tile_store_lower_dev)
 // and Wl holds W = L^{-1} (zeros above the diagonal).  Returns 0,
 // or the 1-based column of the first pivot that is not a positive finite
 // number.  Right-looking by 16-column panels: wave p factors panel p alone
 // (lane r holds row r; pivots broadcast across the wave, no barrier), the
-// trailing lower blocks get the rank-16 update on MFMA.  W follows blockwise:
-// the four 16 x 16 diagonal inverses by column substitution (one lane per
-// column, reusing the pivots' reciprocal square roots), then the 2 x 2 block
-// recursion W21 = -W22 L21 W11, at 16 and at 32, on MFMA.
+// trailing lower blocks get the rank-16 update on MFMA.  This is the chain that
+// every later tile waits for, so W is formed beside it:
+//  - a panel turns a row x of the rows below into x L_pp^{-T}, so with the
+//    identity in S's block (0, p) above the panel (chol_prepare) its first 16
+//    lanes end with L_pp^{-T} = W_pp^T there (panel 0 has no rows above it: wave
+//    1 runs the same panel with the identity below the diagonal block);
+//  - the other blocks follow by rows, W_IJ = -W_II sum_{J <= K < I} L_IK W_KJ, on
+//    MFMA by the waves that the panels leave idle; behind panel 3 only the last
+//    product of the last row remains.
+// Inside the factor kernel (n=16, b=64): panels 2.1 us (the first, cold) and 1.6
+// us, the updates between them 0.6, 0.3 and 0.3 us, the last row of W 0.35 us;
+// 8.6 us in all, 11.4 us with W formed after the panels (3.1 us of it), and
+// the time from one diagonal tile to the next 17.5 -> 15.1 us.
 // Scratch: rinv[64], tmp[4 * 16 * 17].
 // VAR 0: the pivot of column k+1 is broadcast from its updated column entry;
 // VAR 1: lane k+1 forms the next pivot from its own L(k+1,k) (one FMA), so
 // the cross-lane read of L(k+1,k) leaves the pivot chain.  TIMED: thread 0
-// writes s_memrealtime stamps of the phase ends into ts[0..10], and of wave 0's
-// steps inside the diagonal-block inverses into ts[11..13].
-// early_flag (optional): a flag published (agent-scope release, value 1) once
+// writes s_memrealtime stamps of the phase ends into ts[0..8].
+// early_flag (optional): a flag published (device-coherent store, value 1) once
 // panel 0 is done and every wave's earlier global stores are complete, so that
 // stores issued before the call are published off the critical path.
 // Wg (optional): W is also stored to global memory (device coherent, row
-// stride 64): rows 0..31 while the 32-level recursion runs, rows 32..63 at the
-// end; the caller waits for the stores before publishing W.
+// stride 64): rows 0..31 beside panel 3, rows 32..63 at the end; the caller
+// waits for the stores before publishing W.
+__device__ __forceinline__ void chol_prepare(double* S, int tid) {
+  for (int e = tid; e < 3 * 256; e += NT) {
+    const int p = 1 + (e >> 8), row = (e >> 4) & 15, col = e & 15;
+    S[row * LDS_LD + 16 * p + col] = row == col ? 1.0 : 0.0;
+  }
+}
+
 template <int VAR, bool TIMED>
 __device__ __forceinline__ int chol_inv_tile_mfma_t(double* S, double* Wl, double* rinv, double* tmp, int* fail_sh, int tid,
                                                     long long* ts, int* early_flag = nullptr, double* Wg = nullptr) {
-  const int r = tid & 63, q = tid >> 6;
+  int r = tid & 63;
+  const int q = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto Lb = [&](int I, int J) { return S + 16 * I * LDS_LD + 16 * J; };
+  auto Wb = [&](int I, int J) { return Wl + 16 * I * LDS_LD + 16 * J; };
+  auto slot = [&](int J) { return tmp + (1 + J) * 16 * 17; };  // (slot -1: the panels' column buffers)
+  const d4 zero = {0.0, 0.0, 0.0, 0.0};
+  auto lds_done = [&]() {  // this wave's LDS writes are visible to its own reads
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_wave_barrier();
+  };
   if (TIMED && tid == 0) ts[0] = __builtin_amdgcn_s_memrealtime();
-#pragma unroll
+  // one copy of the panel's code for all four: a tile is factored on whichever
+  // workgroup takes its task, with the instructions not yet in its cache
+#pragma unroll 1
   for (int p = 0; p < 4; ++p) {
-    if (p == 0 && q != 0) {
-      // waves 1..3 are idle during panel 0: clear W here (its blocks above the
-      // diagonal stay zero; the diagonal and lower blocks are written below)
-      for (int e = 2 * (tid - 64); e < 64 * 64; e += 2 * (NT - 64))
-        *reinterpret_cast<d2v*>(Wl + (e >> 6) * LDS_LD + (e & 63)) = d2v{0.0, 0.0};
-    }
-    if (q == p) {
+    asm volatile("" : "+v"(r));  // lane offsets formed here, not held across the tile's tasks
+    if (q == p || (p == 0 && q == 1)) {
+      // this lane's row: its own, or (wave 1 beside panel 0) an identity row
+      const int at = (q != p && r >= 16 && r < 32) ? (r - 16) * LDS_LD + 16 : r * LDS_LD + 16 * p;
+      double* const cb0 = tmp + (q == p ? 0 : 128);
       double s[16];
 #pragma unroll
-      for (int m = 0; m < 16; ++m) s[m] = S[r * LDS_LD + 16 * p + m];
+      for (int m = 0; m < 16; ++m) s[m] = S[at + m];
+      if (p == 0) __syncthreads();  // waves 0 and 1 have both read the panel
       double dn = s[0];
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
@@ -493,11 +533,9 @@ __device__ __forceinline__ int chol_inv_tile_mfma_t(double* S, double* Wl, doubl
         const double d = rd_lane(VAR == 1 ? dn : s[m], k);
         // (pivots are checked once after the panels, from rinv)
         const double ri = rsqrt_refined(d);
-        if (r == 0) rinv[k] = ri;
+        if (r == 0 && q == p) rinv[k] = ri;
         // rows below the pivot get L(r,k) = s * ri, the pivot row sqrt(d) = d * ri
-        // (its s is d); rows above hold upper-triangle values that no later step
-        // reads (the trailing updates and broadcasts only use rows > k) and that
-        // are written back as zeros
+        // (its s is d); rows above hold values that no later step reads
         const double lv = s[m] * ri;
         s[m] = lv;
         if (VAR == 1 && m + 1 < 16) dn = __builtin_fma(-lv, lv, s[m + 1]);
@@ -506,21 +544,69 @@ __device__ __forceinline__ int chol_inv_tile_mfma_t(double* S, double* Wl, doubl
         // off the next pivot's critical path)
         if (m + 1 < 16) s[m + 1] -= lv * rd_lane(lv, k + 1);
         if (m + 2 < 16) {
-          double* cb = tmp + (m & 1) * 64;
+          double* cb = cb0 + (m & 1) * 64;
           cb[r] = lv;
 #pragma unroll
           for (int mm = m + 2; mm < 16; ++mm) s[mm] -= lv * cb[16 * p + mm];
         }
       }
-      // the rows above the diagonal keep stale values: nothing reads them, and
-      // the stores of L write zeros there
+      // (the rows above the diagonal block now hold W_pp^T and values that
+      // nothing reads; the stores of L write zeros there)
+      if (q == p) {
 #pragma unroll
-      for (int m = 0; m < 16; ++m) S[r * LDS_LD + 16 * p + m] = s[m];
+        for (int m = 0; m < 16; ++m) S[at + m] = s[m];
+      } else if (r >= 16 && r < 32) {
+#pragma unroll
+        for (int m = 0; m < 16; ++m) Wl[m * LDS_LD + r - 16] = s[m];
+      }
+    } else if (p == 0) {
+      __syncthreads();
+      // waves 2 and 3 clear the blocks of W above the diagonal
+      for (int e = 2 * (tid - 128); e < 64 * 64; e += 256) {
+        const int row = e >> 6, col = e & 63;
+        if (col >= 16 * (row / 16 + 1)) *reinterpret_cast<d2v*>(Wl + row * LDS_LD + col) = d2v{0.0, 0.0};
+      }
+    } else if (p == 1) {
+      if (q == 0) {  // L(1,0) W(0,0)
+        d4 t = zero;
+        mma16x16(t, Lb(1, 0), LDS_LD, Wb(0, 0), LDS_LD, true, 1.0, r);
+        blk_store(t, slot(0), 17, r);
+      }
+    } else if (p == 2) {
+      if (q == 0) {  // W(1,0)
+        d4 t = zero;
+        mma16x16_ta(t, Lb(0, 1), LDS_LD, slot(0), 17, r);
+        blk_store(t, Wb(1, 0), LDS_LD, r);
+      } else if (q == 1) {
+        blk_transpose(Wb(1, 1), Lb(0, 1), r);
+      }
+    } else {
+      // column J = q: W(2,J), then the sum over K of row 3 (slot J)
+      const int J = q;
+      d4 t = zero;
+      if (J < 2) {
+        for (int K = J; K < 2; ++K) mma16x16(t, Lb(2, K), LDS_LD, Wb(K, J), LDS_LD, true, 1.0, r);
+        blk_store(t, slot(J), 17, r);
+        lds_done();
+        t = zero;
+        mma16x16_ta(t, Lb(0, 2), LDS_LD, slot(J), 17, r);
+        blk_store(t, Wb(2, J), LDS_LD, r);
+        lds_done();
+        t = zero;
+        for (int K = J; K < 3; ++K) mma16x16(t, Lb(3, K), LDS_LD, Wb(K, J), LDS_LD, true, 1.0, r);
+      } else {
+        mma16x16(t, Lb(3, 2), LDS_LD, Lb(0, 2), LDS_LD, false, 1.0, r);
+        blk_transpose(Wb(2, 2), Lb(0, 2), r);
+      }
+      blk_store(t, slot(J), 17, r);
+      if (Wg && J == 2) {  // rows 0..31 of W are final
+        for (int row = 0; row < 32; ++row) st_dev(Wg + row * 64 + r, Wl[row * LDS_LD + r]);
+      }
     }
     if (p == 0 && early_flag) __builtin_amdgcn_s_waitcnt(0);  // every wave's earlier stores complete
     __syncthreads();
     if (p == 0 && early_flag && tid == 192)
-      __hip_atomic_store(early_flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(early_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (TIMED && tid == 0) ts[1 + 2 * p] = __builtin_amdgcn_s_memrealtime();
     if (p < 3) {
       // rank-16 update of the trailing lower blocks (I, J), p < J <= I
@@ -530,80 +616,29 @@ __device__ __forceinline__ int chol_inv_tile_mfma_t(double* S, double* Wl, doubl
         while (rem >= 4 - J) { rem -= 4 - J; ++J; }
         const int I = J + rem;
         d4 c;
-        blk_load(c, S + 16 * I * LDS_LD + 16 * J, LDS_LD, r);
-        mma16x16(c, S + 16 * I * LDS_LD + 16 * p, LDS_LD, S + 16 * J * LDS_LD + 16 * p, LDS_LD, false, -1.0, r);
-        blk_store(c, S + 16 * I * LDS_LD + 16 * J, LDS_LD, r);
+        blk_load(c, Lb(I, J), LDS_LD, r);
+        mma16x16(c, Lb(I, p), LDS_LD, Lb(J, p), LDS_LD, false, -1.0, r);
+        blk_store(c, Lb(I, J), LDS_LD, r);
       }
       __syncthreads();
       if (TIMED && tid == 0) ts[2 + 2 * p] = __builtin_amdgcn_s_memrealtime();
     }
   }
-  // ---- W: diagonal 16 x 16 blocks, wave q inverts block q, lane j < 16 computes column j
-  {
-    if (TIMED && tid == 0) ts[11] = __builtin_amdgcn_s_memrealtime();
-    const int Q = q, j = r;
-    double w[16], acc[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      w[i] = ((i == j ? 1.0 : 0.0) - acc[i]) * rinv[16 * Q + i];
-#pragma unroll
-      for (int i2 = i + 1; i2 < 16; ++i2) acc[i2] += S[(16 * Q + i2) * LDS_LD + 16 * Q + i] * w[i];
-    }
-    if (TIMED && tid == 0) ts[12] = __builtin_amdgcn_s_memrealtime();
-    if (j < 16) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) Wl[(16 * Q + i) * LDS_LD + 16 * Q + j] = (i >= j) ? w[i] : 0.0;
-    }
-    if (TIMED && tid == 0) ts[13] = __builtin_amdgcn_s_memrealtime();
-  }
-  __syncthreads();
-  if (TIMED && tid == 0) ts[8] = __builtin_amdgcn_s_memrealtime();
-  // first pivot that is not a positive finite number (checked by wave 2, idle
-  // at level 16): its reciprocal square root is then NaN (d <= 0, NaN or +inf;
-  // zero gives 0 * inf) instead of a positive finite number
-  if (q == 2) {
+  if (q < 3) {  // row 3 of W
+    d4 t = zero;
+    mma16x16_ta(t, Lb(0, 3), LDS_LD, slot(q), 17, r);
+    blk_store(t, Wb(3, q), LDS_LD, r);
+  } else {
+    blk_transpose(Wb(3, 3), Lb(0, 3), r);
+    // first pivot that is not a positive finite number: its reciprocal square
+    // root is then NaN (d <= 0, NaN or +inf; zero gives 0 * inf) instead of a
+    // positive finite number
     const double ri = rinv[r];
     const unsigned long long bad = __builtin_amdgcn_ballot_w64(!(ri > 0.0 && ri < 1.7976931348623157e308));
     if (r == 0) *fail_sh = bad ? __builtin_ctzll(bad) + 1 : 0x7fffffff;
   }
-  // ---- level 16: W(1,0) = -W(1,1) L(1,0) W(0,0) (wave 0), W(3,2) = -W(3,3) L(3,2) W(2,2) (wave 1)
-  if (q < 2) {
-    const int I = 2 * q + 1, J = 2 * q;
-    double* T = tmp + q * 16 * 17;
-    d4 t = {0.0, 0.0, 0.0, 0.0};
-    mma16x16(t, S + 16 * I * LDS_LD + 16 * J, LDS_LD, Wl + 16 * J * LDS_LD + 16 * J, LDS_LD, true, 1.0, r);
-    blk_store(t, T, 17, r);
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    d4 o = {0.0, 0.0, 0.0, 0.0};
-    mma16x16(o, Wl + 16 * I * LDS_LD + 16 * I, LDS_LD, T, 17, true, -1.0, r);
-    blk_store(o, Wl + 16 * I * LDS_LD + 16 * J, LDS_LD, r);
-  }
   __syncthreads();
-  if (TIMED && tid == 0) ts[9] = __builtin_amdgcn_s_memrealtime();
-  // rows 0..31 of W are final: their global stores overlap the 32-level recursion
-  if (Wg) tile_store_rows_dev(Wl, Wg, 64, 0, 32, tid);
-  // ---- level 32: U = L21 W11 (one 16 x 16 block per wave), then W21 = -W22 U
-  {
-    const int I = 2 + (q >> 1), J = q & 1;
-    double* U = tmp + q * 16 * 17;
-    d4 u = {0.0, 0.0, 0.0, 0.0};
-    for (int K = J; K < 2; ++K)
-      mma16x16(u, S + 16 * I * LDS_LD + 16 * K, LDS_LD, Wl + 16 * K * LDS_LD + 16 * J, LDS_LD, true, 1.0, r);
-    blk_store(u, U, 17, r);
-  }
-  __syncthreads();
-  {
-    const int I = 2 + (q >> 1), J = q & 1;
-    d4 o = {0.0, 0.0, 0.0, 0.0};
-    for (int K = 2; K <= I; ++K)
-      mma16x16(o, Wl + 16 * I * LDS_LD + 16 * K, LDS_LD, tmp + (2 * (K - 2) + J) * 16 * 17, 17, true, -1.0, r);
-    blk_store(o, Wl + 16 * I * LDS_LD + 16 * J, LDS_LD, r);
-  }
-  __syncthreads();
-  if (TIMED && tid == 0) ts[10] = __builtin_amdgcn_s_memrealtime();
+  if (TIMED && tid == 0) ts[8] = __builtin_amdgcn_s_memrealtime();
   if (Wg) tile_store_rows_dev(Wl, Wg, 64, 32, 32, tid);
   const int f = *fail_sh;
   return f == 0x7fffffff ? 0 : f;
@@ -656,10 +691,10 @@ __device__ __forceinline__ void trinv_tile(const double* S, double* w, int tid) 
 
 // ---------------------------------------------------------------------------
 // Cross-workgroup completion flags (one int per tile, 0 = pending).  Producer:
-// every wave's stores complete, a barrier, then one thread sets the flag with
-// an agent-scope release.  Consumer: one thread polls with relaxed loads, then
-// an agent-scope acquire makes the producer's writes visible to the whole
-// workgroup (L1 is per CU, L2 per XCD).
+// every wave's device-coherent stores complete, a barrier, then one thread sets
+// the flag.  Consumer: one thread polls, a barrier, then the workgroup reads the
+// data device-coherently (or, through the caches, after an agent-scope acquire:
+// L1 is per CU, L2 per XCD).
 __device__ __forceinline__ bool flag_set(const int* flag) {
   return __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }

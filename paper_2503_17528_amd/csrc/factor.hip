@@ -292,6 +292,13 @@ __host__ __device__ __forceinline__ int ksources(const FactorParams& p, const Ta
   return 0;
 }
 
+// The thread index as a value of its own: the many lane offsets derived from it
+// are formed where they are used, instead of being hoisted out of the ticket
+// loop (or from one part of a task into another) and held in registers.
+__device__ __forceinline__ int fresh(int tid) {
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ long long uni64(long long v) {
   const int lo = __builtin_amdgcn_readfirstlane((int)(unsigned)(v & 0xffffffffLL));
@@ -313,7 +320,7 @@ __device__ __forceinline__ bool wait_ready(const FactorParams& p, const int* f1,
   if (tid == 0) {
     bool ok = spin_wait(f1, p.ctl + CTL_ABORT, p.spin_limit);
     if (ok && f2 != f1) ok = spin_wait(f2, p.ctl + CTL_ABORT, p.spin_limit);
-    acquire_fence();
+    if (p.load == LD_LINE) acquire_fence();
     sh.ok = ok ? 1 : 0;
   }
   __syncthreads();
@@ -334,16 +341,20 @@ __device__ __forceinline__ int extend_ready(const FactorParams& p, const Task& t
   const unsigned long long m = __builtin_amdgcn_ballot_w64(ready);
   const int run = (~m == 0ULL) ? 64 : __builtin_ctzll(~m);
   const int upto = from + run;
-  if (upto > from) acquire_fence();
+  if (upto > from && p.load == LD_LINE) acquire_fence();
   return upto;
 }
 
-// Publish a finished tile: every wave's stores are complete in L2 before the
-// barrier; one agent-scope release then writes the XCD's L2 back and sets the flag.
+// Publish a finished tile: every wave's device-coherent stores are complete
+// before the barrier, and one thread sets the flag.  Everything that another
+// task reads is stored and loaded at device scope, so the flag is a plain
+// device-coherent store (a release would first write the XCD's L2 back) and its
+// readers need no acquire, which would invalidate their caches; only loads
+// through the L2 (LD_LINE) keep the acquire.
 __device__ __forceinline__ void publish(int* flag, int tid) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (tid == 0) __hip_atomic_store(flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Diagonal tile g = (block i, tile column c) and the tile left of it, L(g, g-1).
@@ -409,18 +420,26 @@ __device__ __forceinline__ void diag_partials(const FactorParams& p, const Task&
         __syncthreads();                // everyone's; and stage (kk+1)&1 is no longer read
         const int u = uni(sh.upto);
         upto = u > upto ? u : upto;
-        if (kk + 1 < nk) {
-          KSrc sn;
-          ksources(p, pt, kk + 1, &sn);
-          if (kk + 1 >= upto) {
-            if (!wait_ready(p, sn.fa, sn.fb, sh, tid)) aborted = true;
-            if (rec && tid == 0) rec[7] = __builtin_amdgcn_s_memrealtime();
-            upto = kk + 2;
-          }
+        // the next tiles: loaded under this step's products, or, when they are
+        // not final yet, awaited after them (the products of the last but one
+        // step, 4 us, would otherwise follow the wait, on the chain).  The other
+        // tasks wait first: off the chain a short wait with the load under the
+        // products is the better order (n=128, b=2048 factor 75.5 against 76.0 ms).
+        const bool late = kk + 1 >= upto;
+        KSrc sn;
+        if (kk + 1 < nk) ksources(p, pt, kk + 1, &sn);
+        if (kk + 1 < nk && !late) {
           load_k<F>(p, sh.u.stage[(kk + 1) & 1][0], sn.a, tid);
           load_k<F>(p, sh.u.stage[(kk + 1) & 1][1], sn.b, tid);
         }
         mma_ptile2(acc1, acc2, sh.u.stage[kk & 1][0], sh.u.stage[kk & 1][1], tid);
+        if (kk + 1 < nk && late) {
+          if (!wait_ready(p, sn.fa, sn.fb, sh, tid)) aborted = true;
+          if (rec && tid == 0) rec[7] = __builtin_amdgcn_s_memrealtime();
+          upto = kk + 2;
+          load_k<F>(p, sh.u.stage[(kk + 1) & 1][0], sn.a, tid);
+          load_k<F>(p, sh.u.stage[(kk + 1) & 1][1], sn.b, tid);
+        }
       }
   }
   __builtin_amdgcn_s_waitcnt(0);
@@ -496,6 +515,7 @@ __device__ __forceinline__ void syrk_lower(double* S, const double* X, int tid) 
 // rec (optional): [0] W(g-1) ready, [1] L(g,g-1) published, [2] tile factored.
 __device__ __forceinline__ void diag_finish(const FactorParams& p, int i, int c, Shared& sh, int tid, Acc& acc1,
                                             Acc& acc2, unsigned long long* rec) {
+  tid = fresh(tid);
   const int T = p.T, b = p.b;
   const int64_t bb = (int64_t)b * b;
   const int rows = ext(b, c);
@@ -570,10 +590,15 @@ __device__ __forceinline__ void diag_finish(const FactorParams& p, int i, int c,
     // minus L(g,g-1) L(g,g-1)^T = x x^T on the lower triangle, then publish L(g,g-1)
     // (its barrier also orders these LDS updates before the factorization)
     syrk_lower(sh.u.f.As, sh.u.f.Bs, tid);
+    chol_prepare(sh.u.f.As, tid);
     __syncthreads();  // the updates are in LDS before the factorization reads them
     if (rec && tid == 0) rec[1] = __builtin_amdgcn_s_memrealtime();
+  } else {
+    chol_prepare(sh.u.f.As, tid);
+    __syncthreads();
   }
 
+  tid = fresh(tid);
   // factor and invert A(g,g) - sum over all k < g; L(g,g-1)'s flag is published
   // after the first panel (its stores had that long to complete), and W goes
   // to global memory as its rows become final
@@ -611,8 +636,9 @@ __device__ __forceinline__ void run_diag(const FactorParams& p, const Task& t, S
 
 // One task of one matrix: accumulate, finish, publish.
 template <int F>
-__device__ __forceinline__ void run_task(const FactorParams& p, long long tk, Shared& sh, int tid) {
+__device__ __forceinline__ void run_task(const FactorParams& p, long long tk, Shared& sh, int tid0) {
   {
+    int tid = fresh(tid0);
     Task t = decode(p, tk);
     t.type = uni(t.type); t.i = uni(t.i); t.r = uni(t.r); t.c = uni(t.c);
     unsigned long long tr0 = 0, tr1 = 0;
@@ -748,6 +774,7 @@ __device__ __forceinline__ void run_task(const FactorParams& p, long long tk, Sh
     if (p.trace && tid == 0) tr1 = __builtin_amdgcn_s_memrealtime();
 
     // ---- finish the tile
+    tid = fresh(tid);
     if (t.type == T_TUPD) {
       acc_store_dev(acc, out, 64, 64, 64, 1.0, tid);
     } else if (is_diag) {
@@ -758,6 +785,8 @@ __device__ __forceinline__ void run_task(const FactorParams& p, long long tk, Sh
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
           for (int j = 0; j < 4; ++j) sh.u.f.As[tile_row(tid, bi, j) * LDS_LD + tile_col(tid, bj)] = -acc.v[bi][bj][j];
+      __syncthreads();
+      chol_prepare(sh.u.f.As, tid);
       __syncthreads();
       const int f = uni(chol_inv_tile_mfma(sh.u.f.As, sh.u.f.Bs, sh.rinv, sh.pan, &sh.fail, tid));
       if (f != 0 && f <= rows && tid == 0) {
@@ -1599,17 +1628,15 @@ __device__ void diag_link_probe_body(const double* A, double* Lout, double* Wout
       sh.u.f.As[(idx >> 6) * LDS_LD + (idx & 63)] = v[e];
     }
     __syncthreads();
+    chol_prepare(sh.u.f.As, tid);
+    __syncthreads();
     const long long t0 = __builtin_amdgcn_s_memrealtime();
     f = chol_inv_tile_mfma_t<VAR, true>(sh.u.f.As, sh.u.f.Bs, sh.rinv, sh.pan, &sh.fail, tid, ts);
     __syncthreads();
     const long long t1 = __builtin_amdgcn_s_memrealtime();
     total += t1 - t0;
     if (tid == 0) {
-      for (int k = 0; k < 10; ++k) ph[k] += ts[k + 1] - ts[k];
-      ph[10] += ts[11] - ts[7];  // inside the diagonal-block inverses (wave 0): the pivot check,
-      ph[11] += ts[12] - ts[11];  // the substitution,
-      ph[12] += ts[13] - ts[12];  // the stores of the block row,
-      ph[13] += ts[8] - ts[13];   // and the wait at the barrier
+      for (int k = 0; k < 8; ++k) ph[k] += ts[k + 1] - ts[k];
     }
   }
   for (int e = tid; e < 4096; e += NT) {
