@@ -108,8 +108,14 @@ struct SelinvPlan {
   int64_t chunk;  // blocks per preprocessing chunk
   size_t split_doubles;  // split-k partials of the sweep products (0: no split)
   int split_max;         // largest split count of a sweep product (tuning knob "split")
-  size_t off_W, off_T1, off_PR, off_Xp, off_WT, off_split, bytes;
+  bool sweep;            // the backward sweep is one persistent launch (sweep.hip)
+  size_t off_W, off_T1, off_PR, off_Xp, off_WT, off_split, off_PB, off_sweep, bytes;
 };
+// The backward sweep as one launch: P_B (n-1 blocks), P_R (n arrow blocks) and
+// the V_i (lower, in XD) formed, X_nn in XT; writes XD, XB and XR.
+size_t sweep_work_bytes(int64_t n, int64_t b, int64_t a);
+hipError_t sweep_launch(int64_t n, int64_t b, int64_t a, const double* PB, const double* PR, const double* XT, double* XD,
+                        double* XB, double* XR, void* work, hipStream_t stream);
 // split: reserve the split-k partials of the sweep products (single-matrix
 // calls; the batched selected inversion has parallelism across matrices).
 SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split = true);

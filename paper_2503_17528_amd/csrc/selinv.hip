@@ -177,6 +177,8 @@ static int selinv_split_max(int64_t b, int64_t a) {
   return GEMM_MAX_PROBS;
 }
 
+constexpr int64_t SWEEP_MAX_B = 1024;
+
 SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
   SelinvPlan sp{};
   const int64_t T = (b + 63) / 64;
@@ -196,8 +198,14 @@ SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
   sp.off_PR = take(8 * (size_t)std::max<int64_t>(1, a * b * n));
   sp.off_Xp = take(8 * 2 * bb);  // X_{i+1,i} of two consecutive steps
   sp.off_WT = take(8 * (size_t)std::max<int64_t>(1, 2 * a * a));
+  // One persistent launch for the sweep where its products are too small for
+  // launches of their own, within 2 GiB for all P_B (they then have a place of
+  // their own, as the sweep writes X_{i+1,i} while others still read P_B).
+  sp.sweep = split && n > 1 && b <= SWEEP_MAX_B && (n - 1) * b * b <= (int64_t(2) << 30) / 8;
+  sp.off_PB = take(sp.sweep ? 8 * bb * (size_t)(n - 1) : 8);
+  sp.off_sweep = take(sp.sweep ? sweep_work_bytes(n, b, a) : 8);
   // split-k partial products of the sweep at small b (few output tiles)
-  sp.split_doubles = (split && b <= 1024) ? (size_t)GEMM_MAX_PROBS * bb : 0;
+  sp.split_doubles = (split && !sp.sweep && b <= 1024) ? (size_t)GEMM_MAX_PROBS * bb : 0;
   sp.split_max = selinv_split_max(b, a);
   sp.off_split = take(8 * std::max<size_t>(1, sp.split_doubles));
   sp.bytes = off;
@@ -216,6 +224,42 @@ static std::vector<std::pair<int64_t, int64_t>> selinv_chunks(const SelinvPlan& 
     size = std::min<int64_t>(sp.chunk, 2 * size);
   }
   return c;
+}
+
+// The products of blocks i0 .. i0 + nblk - 1 with their W: P_B into PB (block i0
+// on; P_B = L_{i+1,i} W_i), P_R = L_{n,i} W_i, and V_i = W_i^T W_i (lower) into X_ii.
+static hipError_t block_products(const double* LB, const double* LR, const double* Ws, double* PB, double* PR, double* XD,
+                                 int64_t i0, int nblk, int64_t n, int64_t b, int64_t a, hipStream_t s) {
+  const int64_t bb = b * b, ab = a * b;
+  const int ib = (int)b, ia = (int)a;
+  const int nsub = (int)std::min<int64_t>(nblk, (n - 1) - i0);  // blocks with an L_{i+1,i}
+  GProb pr[3];
+  int np = 0;
+  if (nsub > 0) {
+    GProb p = prob_init();
+    p.seg[0] = seg(LB + i0 * bb, b, 0, Ws, b, 1, ib, TRI_K_GE_COL, bb, bb);
+    p.nseg = 1;
+    p.Cout = PB; p.ldc = b; p.sC0 = bb;
+    p.M = ib; p.N = ib; p.nb0 = nsub;
+    pr[np++] = p;
+  }
+  if (a > 0) {
+    GProb p = prob_init();
+    p.seg[0] = seg(LR + i0 * ab, b, 0, Ws, b, 1, ib, TRI_K_GE_COL, ab, bb);
+    p.nseg = 1;
+    p.Cout = PR + i0 * ab; p.ldc = b; p.sC0 = ab;
+    p.M = ia; p.N = ib; p.nb0 = nblk;
+    pr[np++] = p;
+  }
+  GProb p = prob_init();
+  p.seg[0] = seg(Ws, b, 1, Ws, b, 1, ib, TRI_K_GE_ROW, bb, bb);
+  p.nseg = 1;
+  p.Cout = XD + i0 * bb; p.ldc = b; p.sC0 = bb;
+  p.M = ib; p.N = ib; p.nb0 = nblk;
+  p.lower_tiles = 1;
+  p.store = ST_LOWER;
+  pr[np++] = p;
+  return gemm_launch(pr, np, s);
 }
 
 hipError_t selinv_launch(const SelinvPlan& sp, int64_t n, int64_t b, int64_t a,
@@ -252,6 +296,18 @@ hipError_t selinv_launch(const SelinvPlan& sp, int64_t n, int64_t b, int64_t a,
     BTA_TRY(gemm_launch(&p, 1, s));
   }
 
+  if (sp.sweep && !g_rec) {
+    // ---- all W_i, P_B, P_R and V_i, then the sweep
+    double* PB = reinterpret_cast<double*>(w + sp.off_PB);
+    for (int64_t i0 = 0; i0 < n; i0 += sp.chunk) {
+      const int nblk = (int)std::min<int64_t>(sp.chunk, n - i0);
+      BTA_TRY(fill_zero_launch(Ws, (size_t)bb * nblk, s));
+      BTA_TRY(trtri_batched(LD + i0 * bb, b, bb, Ws, T1, b, bb, ib, nblk, s, 1, 0));
+      BTA_TRY(block_products(LB, LR, Ws, PB + i0 * bb, PR, XD, i0, nblk, n, b, a, s));
+    }
+    return sweep_launch(n, b, a, PB, PR, XT, XD, XB, XR, w + sp.off_sweep, s);
+  }
+
   // ---- per-block preprocessing and the arrow-row recursion on a side
   // stream, chunk by chunk from the last block down, so that the backward
   // sweep (on `s`) can start on the first finished blocks while later chunks
@@ -276,35 +332,7 @@ hipError_t selinv_launch(const SelinvPlan& sp, int64_t n, int64_t b, int64_t a,
     BTA_TRY(fill_zero_launch(Ws, (size_t)bb * nblk, sa));
     BTA_TRY(trtri_batched(LD + i0 * bb, b, bb, Ws, T1, b, bb, ib, nblk, sa, 1, (int)k));
     set_stage(1, (int)k, 100);
-    GProb pr[3];
-    int np = 0;
-    if (nsub > 0) {  // P_B = L_{i+1,i} W_i into the X_{i+1,i} slot
-      GProb p = prob_init();
-      p.seg[0] = seg(LB + i0 * bb, b, 0, Ws, b, 1, ib, TRI_K_GE_COL, bb, bb);
-      p.nseg = 1;
-      p.Cout = inplace ? T1 : XB + i0 * bb; p.ldc = b; p.sC0 = bb;
-      p.M = ib; p.N = ib; p.nb0 = nsub;
-      pr[np++] = p;
-    }
-    if (a > 0) {  // P_R = L_{n,i} W_i
-      GProb p = prob_init();
-      p.seg[0] = seg(LR + i0 * ab, b, 0, Ws, b, 1, ib, TRI_K_GE_COL, ab, bb);
-      p.nseg = 1;
-      p.Cout = PR + i0 * ab; p.ldc = b; p.sC0 = ab;
-      p.M = ia; p.N = ib; p.nb0 = nblk;
-      pr[np++] = p;
-    }
-    {  // V_i = W_i^T W_i (lower) into X_ii
-      GProb p = prob_init();
-      p.seg[0] = seg(Ws, b, 1, Ws, b, 1, ib, TRI_K_GE_ROW, bb, bb);
-      p.nseg = 1;
-      p.Cout = XD + i0 * bb; p.ldc = b; p.sC0 = bb;
-      p.M = ib; p.N = ib; p.nb0 = nblk;
-      p.lower_tiles = 1;
-      p.store = ST_LOWER;
-      pr[np++] = p;
-    }
-    BTA_TRY(gemm_launch(pr, np, sa));
+    BTA_TRY(block_products(LB, LR, Ws, inplace ? T1 : XB + i0 * bb, PR, XD, i0, nblk, n, b, a, sa));
     if (inplace) {  // every L_{i+1,i} of the chunk has been read
       set_stage(1, (int)k, 101);
       BTA_TRY(copy2d_launch(T1, b, bb, XB + i0 * bb, b, bb, ib, ib, nsub, sa));

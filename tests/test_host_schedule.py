@@ -142,3 +142,11 @@ def test_factor_schedule_sub_delays(L, delay, monkeypatch):
         assert L.bta_internal_factor_schedule_check(n, b, a, counts) == 0, (delay, n, b, a)
         T, TA = (b + 63) // 64, (a + 63) // 64
         assert sum(counts) == n * T * (T + 1) // 2 + (n - 1) * T * T + n * T * TA + n * TA * (TA + 1) // 2 + TA * (TA + 1) // 2
+
+
+@pytest.mark.parametrize("n,b,a", [(1, 1, 0), (2, 1, 1), (2, 31, 0), (3, 32, 32), (3, 33, 33), (4, 65, 2), (2, 200, 257),
+                                   (5, 512, 4), (3, 1024, 256)])
+def test_selinv_sweep_tickets(L, n, b, a):
+    """The persistent backward sweep: each 32 x 32 tile once, every wait for a smaller ticket."""
+    L.bta_internal_sweep_check.argtypes = [ctypes.c_int64] * 3
+    assert L.bta_internal_sweep_check(n, b, a) == 0
