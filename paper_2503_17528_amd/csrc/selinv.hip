@@ -177,7 +177,11 @@ static int selinv_split_max(int64_t b, int64_t a) {
   return GEMM_MAX_PROBS;
 }
 
-constexpr int64_t SWEEP_MAX_B = 1024;
+// Largest b of the persistent sweep (us per block, a = 4, product by product
+// against the sweep): b = 384 60 / 30, 512 72 / 40, 640 102 / 71, 768 134 / 119,
+// 1024 220 / 169, 1280 333 / 305, 1536 498 / 556; odd b, with 4-byte operand
+// loads, 641 126 / 101, 1025 295 / 288.
+static int64_t sweep_max_b(int64_t b) { return b % 2 == 0 ? 1280 : 1088; }
 
 SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
   SelinvPlan sp{};
@@ -199,9 +203,9 @@ SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
   sp.off_Xp = take(8 * 2 * bb);  // X_{i+1,i} of two consecutive steps
   sp.off_WT = take(8 * (size_t)std::max<int64_t>(1, 2 * a * a));
   // One persistent launch for the sweep where its products are too small for
-  // launches of their own, within 2 GiB for all P_B (they then have a place of
+  // launches of their own, within 8 GiB for all P_B (they then have a place of
   // their own, as the sweep writes X_{i+1,i} while others still read P_B).
-  sp.sweep = split && n > 1 && b <= SWEEP_MAX_B && (n - 1) * b * b <= (int64_t(2) << 30) / 8;
+  sp.sweep = split && n > 1 && b <= sweep_max_b(b) && (n - 1) * b * b <= (int64_t(8) << 30) / 8;
   sp.off_PB = take(sp.sweep ? 8 * bb * (size_t)(n - 1) : 8);
   sp.off_sweep = take(sp.sweep ? sweep_work_bytes(n, b, a) : 8);
   // split-k partial products of the sweep at small b (few output tiles)

@@ -6,10 +6,13 @@
 //   R(i)  X_{n,i}   = -(X_{n,i+1} P_B + X_nn P_R)
 //   A(i)  X_{i+1,i} = -(X_{i+1,i+1} P_B + X_{n,i+1}^T P_R)
 //   B(i)  X_{i,i}   = V_i - X_{i+1,i}^T P_B - X_{n,i}^T P_R   (lower, mirrored)
-// each cut into 32 x 32 output tiles, one task per tile and workgroup: at b = 512
-// a phase A is 256 tasks, one per CU, where 64 x 64 tiles would be 64.  Launched
-// product by product, a step of b = 512 took 68 us (four launches on the chain
-// besides the copy and the arrow row); here it is two waits.
+// each cut into 32 x 32 output tiles (64 x 64 for larger b), one task per tile and
+// workgroup: at b = 512 a phase A is 256 tasks, one per CU, where 64 x 64 tiles
+// would be 64.  Launched product by product, a step of b = 512 took 68 us (four
+// launches on the chain besides the copy and the arrow row); here it is two
+// waits, 30 us, bound by reading the operands (64 MB of tiles a phase A).  Taking
+// the next ticket while a task runs left ready tasks with busy workgroups (n=256,
+// b=512: 17.1 ms against 10.0).
 //
 // Tasks are taken from an atomic counter in the order R(i), A(i), B(i), i
 // descending, so a task only waits for tasks of smaller tickets, which running
@@ -28,9 +31,6 @@ namespace bta {
 
 namespace {
 
-constexpr int SW = 32;        // output tile edge
-constexpr int SWK = 64;       // k per LDS stage: four sub-stages of 16, one per wave
-constexpr int SUB = SW * 16;  // doubles per operand and sub-stage
 constexpr long long SWEEP_SPIN = 1LL << 22;  // polls before a wait gives up (its tile is then NaN)
 
 struct SweepArgs {
@@ -38,7 +38,8 @@ struct SweepArgs {
   double* XD; double* XB; double* XR;
   int* flags;  // per block: T*T of A, T*T of B, TA*T of R
   int* ctl;    // ticket counter (64 bits), abort flag at ctl[2]
-  int n, b, a, T, TA;
+  int n, b, a, T, TA;  // T, TA: tiles per edge of a block and of the tip
+  int SW;              // tile edge
   long long per_step, ntasks;  // tasks of a step with an A phase; all
 };
 
@@ -110,13 +111,15 @@ __device__ __forceinline__ void sweep_wait(const SweepArgs& p, int64_t f0, int64
     }
 }
 
-// BYTES: operand loads (16, or 4 for operands off 16-byte lines); NS: LDS stages,
-// NS - 1 of them in flight (two with the 4-byte loads: more would outrun the
-// load counter).
-template <int BYTES, int NS>
+// SW: tile edge (wave w takes the quadrant (w / 2, w % 2)).  An LDS stage of 32 KB
+// holds 64 k of a 32-tile, or 32 k of a 64-tile, in sub-stages of 16 k.  BYTES:
+// operand loads (16, or 4 for operands off 16-byte lines); NS: LDS stages, NS - 1
+// of them in flight (two with the 4-byte loads: more would outrun the load counter).
+template <int SW, int BYTES, int NS>
 __global__ __launch_bounds__(256, 1) void selinv_sweep_kernel(SweepArgs p) {
-  constexpr int NI = BYTES == 16 ? 4 : 16, LPS = 2 * NI;  // loads per wave, operand and stage; per wave and stage
-  __shared__ __align__(16) double lds[NS * 8 * SUB];
+  constexpr int WB = SW / 32, SUBS = 4 / WB, SWK = 16 * SUBS, SUB = SW * 16;  // doubles per operand and sub-stage
+  constexpr int NI = WB * (BYTES == 16 ? 4 : 16), LPS = NI * 2 / WB;  // loads per sub-stage operand; per wave and stage
+  __shared__ __align__(16) double lds[NS * 2 * SUBS * SUB];
   __shared__ long long ticket;
   __shared__ int good;
   const int tid0 = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid0 >> 6);
@@ -177,28 +180,45 @@ __global__ __launch_bounds__(256, 1) void selinv_sweep_kernel(SweepArgs p) {
 
     // V's elements of this tile (B), in flight during the wait's barrier
     double* const out = q.kind == SW_R ? p.XR + i * ab : q.kind == SW_A ? p.XB + i * bb : p.XD + i * bb;
-    const int r0 = 16 * (w >> 1), c0 = 16 * (w & 1);
-    d4 v = {0.0, 0.0, 0.0, 0.0};
-    if (q.kind == SW_B) {
+    const int r0 = 16 * WB * (w >> 1), c0 = 16 * WB * (w & 1);
+    d4 v[WB][WB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = r0 + acc_row(lane, j), c = c0 + acc_col(lane);
-        if (r < mext && c < next && n0 + c <= m0 + r) v[j] = ld_dev(out + (int64_t)(m0 + r) * b + n0 + c);
+    for (int x = 0; x < WB; ++x)
+#pragma unroll
+      for (int y = 0; y < WB; ++y) {
+        v[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+        if (q.kind == SW_B) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int r = r0 + 16 * x + acc_row(lane, j), c = c0 + 16 * y + acc_col(lane);
+            if (r < mext && c < next && n0 + c <= m0 + r) v[x][y][j] = ld_dev(out + (int64_t)(m0 + r) * b + n0 + c);
+          }
+        }
       }
-    }
     __syncthreads();
     const bool ok = good != 0;
 
+    // wave w moves both operands of sub-stage w (32-tiles), or operand w % 2 of
+    // sub-stage w / 2 (64-tiles)
+    const int us = w / WB;
     auto issue = [&](int kk) {
       const bool first = kk < nk0;
       const SweepSeg& g = first ? sg[0] : sg[1];
-      const int k = (first ? kk : kk - nk0) * SWK + 16 * w, kext = g.K - k;
-      double* st = lds + (kk % NS) * 8 * SUB + w * 2 * SUB;
-      stage_pieces<SW, NI, BYTES, true>(g.A, g.lda, g.at, 0, mext, k, kext, st, 0, lane);
-      stage_pieces<SW, NI, BYTES, false>(g.B, g.ldb, 1, 0, next, k, kext, st + SUB, 0, lane);
+      const int k = (first ? kk : kk - nk0) * SWK + 16 * us, kext = g.K - k;
+      double* st = lds + ((kk % NS) * SUBS + us) * 2 * SUB;
+      if (WB == 1 || w % 2 == 0) stage_pieces<SW, NI, BYTES, true>(g.A, g.lda, g.at, 0, mext, k, kext, st, 0, lane);
+      if (WB == 1 || w % 2 == 1) stage_pieces<SW, NI, BYTES, false>(g.B, g.ldb, 1, 0, next, k, kext, st + SUB, 0, lane);
     };
-    // two sums (sub-stages 0, 2 and 1, 3): no product waits for the one before it
-    d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+    // 32-tiles: two sums (even and odd sub-stages), so that no product waits for
+    // the one before it
+    constexpr int NA = WB == 1 ? 2 : 1;
+    d4 acc[NA][WB][WB];
+#pragma unroll
+    for (int h = 0; h < NA; ++h)
+#pragma unroll
+      for (int x = 0; x < WB; ++x)
+#pragma unroll
+        for (int y = 0; y < WB; ++y) acc[h][x][y] = d4{0.0, 0.0, 0.0, 0.0};
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // V has landed: the counts below are the stages' alone
     for (int kk = 0; kk < NS - 1 && kk < total; ++kk) issue(kk);
     for (int kk = 0; kk < total; ++kk) {
@@ -206,15 +226,19 @@ __global__ __launch_bounds__(256, 1) void selinv_sweep_kernel(SweepArgs p) {
       else if (NS > 2 && kk + 1 < total) wait_vm_barrier<(NS > 2 ? LPS : 0)>();
       else wait_vm_barrier<0>();
       if (kk + NS - 1 < total) issue(kk + NS - 1);
-      const double* st = lds + (kk % NS) * 8 * SUB;
+      const double* st = lds + (kk % NS) * SUBS * 2 * SUB;
       const int at = kk < nk0 ? sg[0].at : sg[1].at;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        double x[1][4], y[1][4];
-        stage_read<SW, 1>(x, st + u * 2 * SUB, at, r0, lane);
-        stage_read<SW, 1>(y, st + u * 2 * SUB + SUB, 1, c0, lane);
+      for (int u = 0; u < SUBS; ++u) {
+        double x[WB][4], y[WB][4];
+        stage_read<SW, WB>(x, st + u * 2 * SUB, at, r0, lane);
+        stage_read<SW, WB>(y, st + u * 2 * SUB + SUB, 1, c0, lane);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) acc[u & 1] = mfma16(x[0][s], y[0][s], acc[u & 1]);
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int e = 0; e < WB; ++e)
+#pragma unroll
+            for (int f = 0; f < WB; ++f) acc[u % NA][e][f] = mfma16(x[e][s], y[f][s], acc[u % NA][e][f]);
       }
     }
     wait_vm_barrier<0>();  // the stages are read: the tile's image takes their place
@@ -222,15 +246,17 @@ __global__ __launch_bounds__(256, 1) void selinv_sweep_kernel(SweepArgs p) {
     // ---- the tile, through LDS for whole rows (and, mirrored, whole columns)
     constexpr int LDI = SW + 1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const double val = v[j] - (acc[0][j] + acc[1][j]);
-      lds[(r0 + acc_row(lane, j)) * LDI + c0 + acc_col(lane)] = ok ? val : __builtin_nan("");
-    }
-    __syncthreads();
-    const int c = tid & 31;
+    for (int x = 0; x < WB; ++x)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int r = (tid >> 5) + 8 * u;
+      for (int y = 0; y < WB; ++y)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double val = v[x][y][j] - (NA == 2 ? acc[0][x][y][j] + acc[NA - 1][x][y][j] : acc[0][x][y][j]);
+          lds[(r0 + 16 * x + acc_row(lane, j)) * LDI + c0 + 16 * y + acc_col(lane)] = ok ? val : __builtin_nan("");
+        }
+    __syncthreads();
+    const int c = tid % SW;
+    for (int r = tid / SW; r < SW; r += 256 / SW) {
       if (q.kind != SW_B) {
         if (r < mext && c < next) st_dev(out + (int64_t)(m0 + r) * b + n0 + c, lds[r * LDI + c]);
       } else if (q.m == q.n) {
@@ -251,11 +277,17 @@ __global__ __launch_bounds__(256) void sweep_reset_kernel(int* p, int64_t count)
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256) p[e] = 0;
 }
 
+// Tile edge 64 from this b on: at 32 a phase reads its operands twice as often and,
+// at b = 768, needs three rounds of the CUs (us per block with 32 / 64: b = 512
+// 40 / 72, 640 71 / 96, 768 124 / 119, 1024 210 / 169).
+constexpr int64_t SWEEP_WIDE_B = 768;
+
 SweepArgs sweep_args(int64_t n, int64_t b, int64_t a) {
   SweepArgs p{};
   p.n = (int)n; p.b = (int)b; p.a = (int)a;
-  p.T = (int)((b + SW - 1) / SW);
-  p.TA = (int)((a + SW - 1) / SW);
+  p.SW = b >= SWEEP_WIDE_B ? 64 : 32;
+  p.T = (int)((b + p.SW - 1) / p.SW);
+  p.TA = (int)((a + p.SW - 1) / p.SW);
   const long long nr = (long long)p.TA * p.T, nb = (long long)p.T * (p.T + 1) / 2;
   p.per_step = nr + (long long)p.T * p.T + nb;
   p.ntasks = nr + nb + (n - 1) * p.per_step;
@@ -295,10 +327,9 @@ hipError_t sweep_launch(int64_t n, int64_t b, int64_t a, const double* PB, const
   const bool pairs = b % 2 == 0 && a % 2 == 0 && al(PB) && al(PR) && al(XT) && al(XD) && al(XB) && al(XR);
   const long long grid = std::min<long long>(p.ntasks, std::max(1, device_cu_count()));
   timing_mark(KT_GEMM, true, s);
-  if (pairs)
-    hipLaunchKernelGGL((selinv_sweep_kernel<16, 4>), dim3((unsigned)grid), dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL((selinv_sweep_kernel<4, 2>), dim3((unsigned)grid), dim3(256), 0, s, p);
+  auto kernel = p.SW == 64 ? (pairs ? selinv_sweep_kernel<64, 16, 4> : selinv_sweep_kernel<64, 4, 2>)
+                           : (pairs ? selinv_sweep_kernel<32, 16, 4> : selinv_sweep_kernel<32, 4, 2>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, s, p);
   timing_mark(KT_GEMM, false, s);
   return hipGetLastError();
 }

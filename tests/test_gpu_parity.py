@@ -81,6 +81,22 @@ def test_odd_extents(torch_cuda, n, b, a):
     test_factor_selinv_parity(torch_cuda, n, b, a)
 
 
+@pytest.mark.parametrize("n,b,a", [(2, 31, 33), (5, 32, 2), (4, 96, 32), (3, 766, 4), (3, 768, 2), (3, 769, 65), (2, 1088, 130),
+                                   (2, 1087, 3)])
+def test_sweep_tiles(torch_cuda, n, b, a):
+    """The persistent backward sweep at the edges of its 32- and 64-tiles, with
+    16- and 4-byte operand loads, out of place and in place."""
+    test_factor_selinv_parity(torch_cuda, n, b, a)
+    from paper_2503_17528_amd import bta
+
+    Q = synth.make_np(synth.workload(n, b, a), 3)
+    L = bta.factor(*to_dev(Q))[:4]
+    X = bta.selinv(*L)
+    Y = bta.selinv(*L, out=L)  # in place
+    for x, y in zip(X, Y):
+        assert torch_cuda.equal(x, y)
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("n,b,a", [(3, 384, 6), (2, 520, 8), (4, 136, 2), (2, 64, 130), (5, 192, 0)])
 def test_selinv_gemm_kernels(torch_cuda, n, b, a, mode):

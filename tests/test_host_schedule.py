@@ -145,8 +145,8 @@ def test_factor_schedule_sub_delays(L, delay, monkeypatch):
 
 
 @pytest.mark.parametrize("n,b,a", [(1, 1, 0), (2, 1, 1), (2, 31, 0), (3, 32, 32), (3, 33, 33), (4, 65, 2), (2, 200, 257),
-                                   (5, 512, 4), (3, 1024, 256)])
+                                   (5, 512, 4), (3, 767, 3), (3, 768, 64), (3, 1024, 256), (3, 1280, 65)])
 def test_selinv_sweep_tickets(L, n, b, a):
-    """The persistent backward sweep: each 32 x 32 tile once, every wait for a smaller ticket."""
+    """The persistent backward sweep: each 32 x 32 (64 x 64) tile once, every wait for a smaller ticket."""
     L.bta_internal_sweep_check.argtypes = [ctypes.c_int64] * 3
     assert L.bta_internal_sweep_check(n, b, a) == 0
