@@ -387,6 +387,11 @@ __device__ __forceinline__ long long chain_ticket(const ChainArgs& p, long long*
   return ((long long)hi << 32) | (unsigned)lo;
 }
 
+// p[0] + p[step] + ... + p[7 step], pairwise
+__device__ __forceinline__ double sum8(const double* p, int step) {
+  return ((p[0] + p[step]) + (p[2 * step] + p[3 * step])) + ((p[4 * step] + p[5 * step]) + (p[6 * step] + p[7 * step]));
+}
+
 constexpr long long CHAIN_SPIN = 1LL << 22;  // polls before a wait gives up (its outputs are then NaN)
 
 __device__ __forceinline__ bool chain_aborted(const ChainArgs& p) {
@@ -414,7 +419,7 @@ __global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
     const int64_t ra = std::min<int64_t>(q.r0 + 2 * w, p.b - 1), rb = std::min<int64_t>(q.r0 + 2 * w + 1, p.b - 1);
     const int64_t cc = std::min<int64_t>(q.r0 + (tid & 15), p.b - 1);
     const int rg = tid >> 4;
-    double m[32], s0 = 0.0, s1 = 0.0;
+    double m[32], sum[4] = {0.0, 0.0, 0.0, 0.0};  // four short sums per thread, then trees
     for (int64_t kc = q.k0; kc < q.k1; kc += KC) {
       const int64_t left = q.k1 - kc;
       if constexpr (!BWD) {
@@ -453,30 +458,27 @@ __global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
           const bool in = 64 * c + lane < left;
-          s0 = __builtin_fma(in ? m[c] : 0.0, xs[64 * c + lane], s0);
-          s1 = __builtin_fma(in ? m[16 + c] : 0.0, xs[64 * c + lane], s1);
+          sum[c & 1] = __builtin_fma(in ? m[c] : 0.0, xs[64 * c + lane], sum[c & 1]);
+          sum[2 + (c & 1)] = __builtin_fma(in ? m[16 + c] : 0.0, xs[64 * c + lane], sum[2 + (c & 1)]);
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < 32; ++j) s0 = __builtin_fma(rg + 32 * j < left ? m[j] : 0.0, xs[rg + 32 * j], s0);
+        for (int j = 0; j < 32; ++j)
+          sum[j & 3] = __builtin_fma(rg + 32 * j < left ? m[j] : 0.0, xs[rg + 32 * j], sum[j & 3]);
       }
     }
     if constexpr (!BWD) {
-      s0 = wave_sum(s0);
-      s1 = wave_sum(s1);
+      const double s0 = wave_sum(sum[0] + sum[1]), s1 = wave_sum(sum[2] + sum[3]);
       if (lane < 2) red[2 * w + lane] = lane ? s1 : s0;
     } else {
+      double s0 = (sum[0] + sum[1]) + (sum[2] + sum[3]);
       s0 += __shfl_xor(s0, 16, 64);
       s0 += __shfl_xor(s0, 32, 64);
       if (lane < 16) red[16 * w + lane] = s0;
     }
     __syncthreads();
     if (tid < SOLVE_ROWS && q.r0 + tid < p.b) {
-      double v = red[tid];
-      if constexpr (BWD) {
-#pragma unroll
-        for (int u = 1; u < 8; ++u) v += red[16 * u + tid];
-      }
+      double v = BWD ? sum8(red + tid, 16) : red[tid];
       const int64_t e = q.g * p.N + q.out + q.r0 + tid;
       if (q.base) v = q.base[e] - v;
       if (__builtin_bit_cast(unsigned long long, v) == SOLVE_PENDING)
@@ -487,8 +489,7 @@ __global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
 }
 
 // Sixteen right-hand sides per group on MFMA: a task's 16 x 16 output is
-// accumulated by eight waves, each a share of the k range, and summed in wave
-// order.  Readiness is a flag per task: a poll of every element, as for one
+// accumulated by eight waves, each a share of the k range, and summed pairwise.  Readiness is a flag per task: a poll of every element, as for one
 // right-hand side, would repeat 128 bytes per row.
 template <bool BWD>
 __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
@@ -507,7 +508,7 @@ __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
     const double* M = q.M + (BWD ? rm : rm * p.b);
     struct __attribute__((packed, aligned(8))) Row4 { d4 v; };  // four k of a row, any 8-byte alignment
     bool ok = true;
-    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    d4 acc[2 * Q] = {};  // two chains per group of k: short sums, added pairwise at the end
     for (int64_t kc = q.k0; kc < q.k1; kc += KC) {
       double a[Q][4], v[Q][4];
 #pragma unroll
@@ -554,16 +555,16 @@ __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const bool in = kc + 16 * (w + 8 * u) + g4 + j < q.k1;
-          acc = mfma16(in ? a[u][j] : 0.0, in ? v[u][j] : 0.0, acc);
+          acc[2 * u + (j & 1)] = mfma16(in ? a[u][j] : 0.0, in ? v[u][j] : 0.0, acc[2 * u + (j & 1)]);
         }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) red[w * 256 + acc_row(lane, j) * 16 + acc_col(lane)] = acc[j];
+    for (int j = 0; j < 4; ++j)
+      red[w * 256 + acc_row(lane, j) * 16 + acc_col(lane)] = ((acc[0][j] + acc[1][j]) + (acc[2][j] + acc[3][j])) +
+                                                             ((acc[4][j] + acc[5][j]) + (acc[6][j] + acc[7][j]));
     __syncthreads();
     if (tid < 256 && q.r0 + (tid >> 4) < p.b) {
-      double v = red[tid];
-#pragma unroll
-      for (int u = 1; u < 8; ++u) v += red[256 * u + tid];
+      double v = sum8(red + tid, 256);
       const int64_t e = (q.g * p.N + q.out + q.r0) * 16 + tid;
       if (q.base) v = q.base[e] - v;
       st_dev(q.ob + e, ok ? v : __builtin_nan(""));
