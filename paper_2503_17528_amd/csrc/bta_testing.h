@@ -99,6 +99,9 @@ BTA_TESTING_API int bta_internal_tune_clear(void);
  * every tile is produced once and every wait is for a smaller ticket. */
 BTA_TESTING_API int bta_internal_sweep_check(int64_t n, int64_t b, int64_t a);
 
+/* Right-hand sides per group of a solve, 1 or 16 (solve.hip). */
+BTA_TESTING_API int bta_internal_solve_group(int64_t n, int64_t b, int64_t a, int64_t nrhs);
+
 /* ---- GEMM engine and measurement (gemm.hip) */
 /* GEMM kernel family of the selected inversion (0 automatic, 1 4-byte operand
  * loads, 2 16-byte ones where allowed, 3, 5 64 x 64 and 4, 6, 7 128 x 128 tiles); returns the

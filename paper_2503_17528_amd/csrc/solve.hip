@@ -13,6 +13,7 @@
 
 #include "bta_device.hpp"
 #include "bta_internal.hpp"
+#include "bta_testing.h"
 
 namespace bta {
 
@@ -306,12 +307,25 @@ static hipError_t transpose_launch(const double* src, int64_t lds, int64_t ss, d
 }
 
 // ---------------------------------------------------------------- the chain of blocks
-// Right-hand sides travel in groups of NR: NR = 1 (vector FMAs) for at most
-// SOLVE_SINGLE of them, else 16 (one MFMA column block).  Element e of right-hand
-// side j is at ((j / NR) N + e) NR + j % NR, so a group is one array of rows.
-constexpr int64_t SOLVE_SINGLE = 4;
-constexpr int SOLVE_ROWS = 16;  // rows of a block's vector per task
-static int solve_group(int64_t nrhs) { return nrhs <= SOLVE_SINGLE ? 1 : 16; }
+// Right-hand sides travel in groups of NR: 1 (vector FMAs) or 16 (one MFMA column
+// block).  Element e of right-hand side j is at ((j / NR) N + e) NR + j % NR, so a
+// group is one array of rows.  A phase of single groups is shorter (its tasks hand
+// elements on, not flags) until their tasks, ceil(b / 16) per right-hand side,
+// outnumber the CUs.  Solves with single / sixteen-wide groups (ms): 400 blocks of
+// b = 64, 32 right-hand sides (128 tasks a phase) 4.2 / 6.2, 64 (256) 7.2 / 6.2; 256
+// of b = 256, 8 (128) 3.1 / 4.3, 12 (192) 4.3 / 4.3, 16 (256) 5.1 / 4.3; 128 of b =
+// 512, 5 (160) 2.5 / 2.7, 8 (256) 3.1 / 2.7; 64 of b = 1024, 4 (256) 2.6 / 3.3, 8
+// (512) 4.0 / 3.3; 32 of b = 2048, 2 (256) 4.2 / 5.2, 4 (512) 5.3 / 5.2.  Single
+// groups keep several copies of the vectors, so above SOLVE_SINGLE of them only
+// where a copy is small.
+constexpr int64_t SOLVE_SINGLE = 4;           // right-hand sides that always go singly
+constexpr int64_t SOLVE_SINGLE_TASKS = 192;   // tasks of a phase up to which more of them do
+constexpr int64_t SOLVE_SINGLE_SIZE = int64_t(1) << 25;  // and elements of all of them
+constexpr int SOLVE_ROWS = 16;                // rows of a block's vector per task
+static int solve_group(int64_t b, int64_t N, int64_t nrhs) {
+  const bool few = nrhs * ((b + SOLVE_ROWS - 1) / SOLVE_ROWS) <= SOLVE_SINGLE_TASKS && nrhs * N <= SOLVE_SINGLE_SIZE;
+  return nrhs <= SOLVE_SINGLE || few ? 1 : 16;
+}
 __host__ __device__ inline int64_t rhs_at(int64_t j, int64_t e, int64_t N, int NR) { return (j / NR * N + e) * NR + j % NR; }
 
 // A vector element that no task has written yet (one NaN; a result with the
@@ -665,7 +679,7 @@ static SolvePlan solve_plan(int64_t n, int64_t b, int64_t a, int64_t nrhs) {
   sp.C1 = std::min(sp.C1, sp.C);
   sp.nchunks = (n + sp.C - 1) / sp.C;
   const int64_t N = n * b + a;
-  sp.NR = solve_group(nrhs);
+  sp.NR = solve_group(b, N, nrhs);
   sp.NG = (nrhs + sp.NR - 1) / sp.NR;
   sp.S = (int)((b + SOLVE_ROWS - 1) / SOLVE_ROWS);
   const int64_t nv = sp.NG * N * sp.NR;
@@ -787,3 +801,8 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
 }
 
 }  // namespace bta
+
+// Right-hand sides per group of a solve (1 or 16).
+BTA_TESTING_API int bta_internal_solve_group(int64_t n, int64_t b, int64_t a, int64_t nrhs) {
+  return bta::solve_group(b, n * b + a, nrhs);
+}

@@ -206,6 +206,13 @@ def test_solve_groups(torch_cuda, n, b, a, nrhs):
     test_solve_and_logdet(torch_cuda, n, b, a, nrhs)
 
 
+# the same with more right-hand sides: singly up to 192 tasks of 16 rows a phase, else 16 wide
+@pytest.mark.parametrize("n,b,a,nrhs", [(2, 16, 3, 192), (2, 16, 3, 193), (3, 17, 0, 97), (3, 1, 1, 200), (2, 512, 5, 6),
+                                        (2, 511, 129, 7), (4, 256, 2, 12)])
+def test_solve_group_edges(torch_cuda, n, b, a, nrhs):
+    test_solve_and_logdet(torch_cuda, n, b, a, nrhs)
+
+
 @pytest.mark.parametrize("nrhs", [1, 6])
 def test_solve_chunks(torch_cuda, nrhs):
     """More blocks than inverses fit in the workspace at once (14 of 4096: two

@@ -150,3 +150,14 @@ def test_selinv_sweep_tickets(L, n, b, a):
     """The persistent backward sweep: each 32 x 32 (64 x 64) tile once, every wait for a smaller ticket."""
     L.bta_internal_sweep_check.argtypes = [ctypes.c_int64] * 3
     assert L.bta_internal_sweep_check(n, b, a) == 0
+
+
+# n, b, nrhs and the faster group width there (n = 1 << 24: the vectors' size decides)
+@pytest.mark.parametrize("n,b,nrhs,group", [(400, 64, 16, 1), (400, 64, 32, 1), (400, 64, 64, 16), (2000, 33, 5, 1),
+                                            (300, 128, 32, 16), (256, 256, 5, 1), (256, 256, 8, 1), (256, 256, 16, 16),
+                                            (128, 512, 5, 1), (128, 512, 8, 16), (64, 1024, 4, 1), (64, 1024, 5, 16),
+                                            (1 << 24, 2, 4, 1), (1 << 24, 2, 5, 16)])
+def test_solve_group_width(L, n, b, nrhs, group):
+    """Right-hand sides per group of the solve, on both sides of its rule."""
+    L.bta_internal_solve_group.argtypes = [ctypes.c_int64] * 4
+    assert L.bta_internal_solve_group(n, b, 4, nrhs) == group
