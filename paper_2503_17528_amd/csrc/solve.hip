@@ -341,12 +341,17 @@ constexpr unsigned long long SOLVE_PENDING = 0x7ff8b17ab17ab17aULL;
 // are resident.  A task's matrix elements do not depend on the chain and are
 // loaded before its wait; the transposed products read the matrix as it lies,
 // SOLVE_ROWS columns (a cache line) per task.
+//
+// Groups of 16 work in place: z (x) takes the place of y's rows, which only the
+// same rows' task of phase 0 reads, before them, and t is one block's, as every
+// task of the next block's phase 0 waits for all of phase 1.  Single vectors
+// carry their readiness, so y, t and z are arrays of their own.
 struct ChainArgs {
   const double* LB; const double* W;  // W of block i0 on
-  const double* y; double* t; double* z;  // phase 0 input, phase 0 and 1 outputs (groups of N, N, N rows)
+  const double* y; double* t; double* z;  // phase 0 input, phase 0 and 1 outputs (groups of N, Nt, N rows)
   int* flags;                         // NR = 16: [block][phase][group][task]
   int* ctl;                           // ticket counter (64 bits), abort flag at ctl[2]
-  int64_t n, b, N, i0, i1;
+  int64_t n, b, N, Nt, i0, i1;           // Nt: N, or b (groups of 16: one block's t)
   int S, NG;                          // tasks per phase and group, groups
   long long ntasks;
 };
@@ -354,12 +359,11 @@ struct ChainArgs {
 struct ChainTask {
   int64_t i, r0, k0, k1;  // block, first row, k range
   const double* M;        // matrix (nullptr: empty k range)
-  int64_t x, out;         // element offsets of x's and the output's block
-  const double* xb; const double* base; double* ob;
+  const double* x; const double* base; double* out;  // the group's rows of x's, y's (or null) and the output's block
   int s, g, ph;
 };
 
-template <bool BWD>
+template <bool BWD, int NR>
 __device__ __forceinline__ ChainTask chain_task(const ChainArgs& p, long long t) {
   ChainTask k;
   const long long per = (long long)p.S * p.NG, q = t / per;
@@ -370,24 +374,23 @@ __device__ __forceinline__ ChainTask chain_task(const ChainArgs& p, long long t)
   k.i = BWD ? p.i1 - 1 - (q >> 1) : p.i0 + (q >> 1);
   k.r0 = (int64_t)SOLVE_ROWS * k.s;
   const int64_t bb = p.b * p.b;
-  k.out = k.i * p.b;
+  const int64_t at = (k.g * p.N + k.i * p.b) * NR;
+  double* const tb = p.t + (k.g * p.Nt + (NR == 1 ? k.i * p.b : 0)) * NR;
   if (k.ph == 0) {
     const bool has = BWD ? k.i < p.n - 1 : k.i > 0;
     k.M = has ? p.LB + (BWD ? k.i : k.i - 1) * bb : nullptr;
-    k.x = (BWD ? k.i + 1 : k.i - 1) * p.b;
+    k.x = p.z + at + (has ? (BWD ? p.b : -p.b) * NR : 0);
     k.k0 = 0;
     k.k1 = has ? p.b : 0;
-    k.xb = p.z;
-    k.ob = p.t;
-    k.base = p.y;
+    k.base = p.y + at;
+    k.out = tb;
   } else {
     k.M = p.W + (k.i - p.i0) * bb;
-    k.x = k.out;
+    k.x = tb;
     k.k0 = BWD ? k.r0 : 0;
     k.k1 = BWD ? p.b : std::min<int64_t>(p.b, k.r0 + SOLVE_ROWS);
-    k.xb = p.t;
-    k.ob = p.z;
     k.base = nullptr;
+    k.out = p.z + at;
   }
   return k;
 }
@@ -426,8 +429,8 @@ __global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
   for (;;) {
     const long long tk = chain_ticket(p, &ticket, tid);
     if (tk >= p.ntasks) break;
-    const ChainTask q = chain_task<BWD>(p, tk);
-    const double* x = q.xb + q.g * p.N + q.x;
+    const ChainTask q = chain_task<BWD, 1>(p, tk);
+    const double* x = q.x;
     // forward: rows 2w, 2w + 1 of the task, lanes along k; backward: column
     // tid % 16, rows tid / 16 + 32 j
     const int64_t ra = std::min<int64_t>(q.r0 + 2 * w, p.b - 1), rb = std::min<int64_t>(q.r0 + 2 * w + 1, p.b - 1);
@@ -493,18 +496,18 @@ __global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
     __syncthreads();
     if (tid < SOLVE_ROWS && q.r0 + tid < p.b) {
       double v = BWD ? sum8(red + tid, 16) : red[tid];
-      const int64_t e = q.g * p.N + q.out + q.r0 + tid;
-      if (q.base) v = q.base[e] - v;
+      if (q.base) v = q.base[q.r0 + tid] - v;
       if (__builtin_bit_cast(unsigned long long, v) == SOLVE_PENDING)
         v = __builtin_bit_cast(double, SOLVE_PENDING ^ 1ULL);
-      st_dev(q.ob + e, v);
+      st_dev(q.out + q.r0 + tid, v);
     }
   }
 }
 
 // Sixteen right-hand sides per group on MFMA: a task's 16 x 16 output is
-// accumulated by eight waves, each a share of the k range, and summed pairwise.  Readiness is a flag per task: a poll of every element, as for one
-// right-hand side, would repeat 128 bytes per row.
+// accumulated by eight waves, each a share of the k range, and summed pairwise.
+// Readiness is a flag per task: a poll of every element, as for one right-hand
+// side, would repeat 128 bytes per row.
 template <bool BWD>
 __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
   constexpr int KC = 512, Q = KC / 128;  // k per chunk, groups of 16 k per wave
@@ -516,11 +519,13 @@ __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
   for (;;) {
     const long long tk = chain_ticket(p, &ticket, tid);
     if (tk >= p.ntasks) break;
-    const ChainTask q = chain_task<BWD>(p, tk);
-    const double* x = q.xb + (q.g * p.N + q.x) * 16;
+    const ChainTask q = chain_task<BWD, 16>(p, tk);
+    const double* x = q.x;
     const int64_t rm = std::min<int64_t>(q.r0 + mn, p.b - 1);
     const double* M = q.M + (BWD ? rm : rm * p.b);
     struct __attribute__((packed, aligned(8))) Row4 { d4 v; };  // four k of a row, any 8-byte alignment
+    const bool live = tid < 256 && q.r0 + (tid >> 4) < p.b;
+    const double base = live && q.base ? ld_dev(q.base + q.r0 * 16 + tid) : 0.0;
     bool ok = true;
     d4 acc[2 * Q] = {};  // two chains per group of k: short sums, added pairwise at the end
     for (int64_t kc = q.k0; kc < q.k1; kc += KC) {
@@ -577,11 +582,10 @@ __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
       red[w * 256 + acc_row(lane, j) * 16 + acc_col(lane)] = ((acc[0][j] + acc[1][j]) + (acc[2][j] + acc[3][j])) +
                                                              ((acc[4][j] + acc[5][j]) + (acc[6][j] + acc[7][j]));
     __syncthreads();
-    if (tid < 256 && q.r0 + (tid >> 4) < p.b) {
+    if (live) {
       double v = sum8(red + tid, 256);
-      const int64_t e = (q.g * p.N + q.out + q.r0) * 16 + tid;
-      if (q.base) v = q.base[e] - v;
-      st_dev(q.ob + e, ok ? v : __builtin_nan(""));
+      if (q.base) v = base - v;
+      st_dev(q.out + q.r0 * 16 + tid, ok ? v : __builtin_nan(""));
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -594,17 +598,18 @@ __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
   }
 }
 
-// The right-hand sides into groups (padded with zero columns), the vectors of
-// both sweeps to pending, and the flags and ticket counters to zero.
+// The right-hand sides into groups (padded with zero columns), the forward
+// sweep's vectors to pending (single groups), and the flags and ticket counters
+// to zero.
 __global__ __launch_bounds__(256) void solve_gather_kernel(const double* rhs, int64_t nrhs, int64_t N, int NR, int64_t NG,
-                                                           double* y, unsigned long long* pend, int64_t npend, int* zero,
-                                                           int64_t nzero) {
+                                                           double* y, unsigned long long* t, unsigned long long* z, int64_t npend,
+                                                           int* zero, int64_t nzero) {
   const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
   for (int64_t e = t0; e < NG * N * NR; e += step) {
     const int64_t row = e / NR, j = row / N * NR + e % NR;
     y[e] = j < nrhs ? rhs[row % N * nrhs + j] : 0.0;
   }
-  for (int64_t e = t0; e < npend; e += step) pend[e] = SOLVE_PENDING;
+  for (int64_t e = t0; e < npend; e += step) t[e] = z[e] = SOLVE_PENDING;
   for (int64_t e = t0; e < nzero; e += step) zero[e] = 0;
 }
 __global__ __launch_bounds__(256) void solve_scatter_kernel(double* rhs, int64_t nrhs, int64_t N, int64_t nb, int NR,
@@ -657,17 +662,21 @@ __global__ __launch_bounds__(256) void solve_tip_rhs_kernel(const double* y, int
 }
 
 // z(j)[i*b + c] -= sum_{r<a} L_{n,i}[r][c] x_n(j)[r] for every block i < n
-// (the arrow terms of the backward sweep: x_n is final before it starts).
+// (the arrow terms of the backward sweep: x_n is final before it starts), and
+// that sweep's vectors to pending where they carry their readiness (t and x, not
+// null: the same places as the forward sweep's t and y, which it is done with).
 __global__ __launch_bounds__(256) void solve_arrow_terms_kernel(const double* LR, int64_t n, int64_t b, int64_t a,
-                                                                const double* xn, int64_t nrhs, int64_t N, int NR, double* z) {
+                                                                const double* xn, int64_t nrhs, int64_t N, int NR, double* z,
+                                                                unsigned long long* t, unsigned long long* x) {
   const int64_t g = blockIdx.y;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n * b * NR; e += (int64_t)gridDim.x * 256) {
     const int64_t row = e / NR, j = g * NR + e % NR, i = row / b, c = row - i * b;
-    if (j >= nrhs) continue;
+    if (t) t[g * N + row] = x[g * N + row] = SOLVE_PENDING;
+    if (j >= nrhs || a == 0) continue;
     const double* M = LR + i * a * b + c;
-    const double* x = xn + j * a;
+    const double* xt = xn + j * a;
     double acc = 0.0;
-    for (int64_t r = 0; r < a; ++r) acc = __builtin_fma(M[r * b], x[r], acc);
+    for (int64_t r = 0; r < a; ++r) acc = __builtin_fma(M[r * b], xt[r], acc);
     z[g * N * NR + e] -= acc;
   }
 }
@@ -677,9 +686,9 @@ __global__ __launch_bounds__(256) void solve_arrow_terms_kernel(const double* LR
 // (C1 blocks at a time), else chunks; the backward sweep then forms all but the
 // last one again.
 struct SolvePlan {
-  int64_t C, C1, nchunks, NG, npend, nzero;
+  int64_t C, C1, nchunks, NG, Nt, npend, nzero;
   int NR, S;
-  size_t off_W, off_T1, off_WT, off_WTt, off_y, off_pend, off_zero, off_t, off_t2, off_xn, off_ptip, bytes;
+  size_t off_W, off_T1, off_WT, off_WTt, off_y, off_t, off_z, off_zero, off_tb, off_t2, off_xn, off_ptip, bytes;
 };
 
 static SolvePlan solve_plan(int64_t n, int64_t b, int64_t a, int64_t nrhs) {
@@ -695,7 +704,8 @@ static SolvePlan solve_plan(int64_t n, int64_t b, int64_t a, int64_t nrhs) {
   sp.NG = (nrhs + sp.NR - 1) / sp.NR;
   sp.S = (int)((b + SOLVE_ROWS - 1) / SOLVE_ROWS);
   const int64_t nv = sp.NG * N * sp.NR;
-  sp.npend = 4 * nv;  // t and the result of each sweep
+  sp.Nt = sp.NR > 1 ? b : N;
+  sp.npend = sp.NR > 1 ? 0 : nv;  // elements of t and of z that start as pending
   // per sweep and chunk a ticket counter and an abort flag (4 ints), then the flags of both sweeps
   sp.nzero = 8 * sp.nchunks + (sp.NR > 1 ? 4 * n * sp.NG * sp.S : 0);
   size_t off = 0;
@@ -705,9 +715,10 @@ static SolvePlan solve_plan(int64_t n, int64_t b, int64_t a, int64_t nrhs) {
   sp.off_WT = take(8 * (size_t)(a * a));
   sp.off_WTt = take(8 * (size_t)(a * a));
   sp.off_y = take(8 * (size_t)nv);
-  sp.off_pend = take(8 * (size_t)sp.npend);
+  sp.off_t = take(8 * (size_t)(sp.NG * sp.Nt * sp.NR));
+  sp.off_z = sp.NR > 1 ? sp.off_y : take(8 * (size_t)nv);
   sp.off_zero = take(4 * (size_t)sp.nzero);
-  sp.off_t = take(8 * (size_t)(a * nrhs));
+  sp.off_tb = take(8 * (size_t)(a * nrhs));
   sp.off_t2 = take(8 * (size_t)(a * nrhs));
   sp.off_xn = take(8 * (size_t)(a * nrhs));
   sp.off_ptip = take(8 * (size_t)(n * a * sp.NG * sp.NR));
@@ -723,17 +734,18 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
   char* w = static_cast<char*>(work);
   auto at = [&](size_t off) { return reinterpret_cast<double*>(w + off); };
   double *W = at(sp.off_W), *T1 = at(sp.off_T1), *WT = at(sp.off_WT), *WTt = at(sp.off_WTt), *y = at(sp.off_y);
-  double *tb = at(sp.off_t), *t2 = at(sp.off_t2), *xn = at(sp.off_xn), *ptip = at(sp.off_ptip);
+  double *tb = at(sp.off_tb), *t2 = at(sp.off_t2), *xn = at(sp.off_xn), *ptip = at(sp.off_ptip);
   const int64_t N = n * b + a, bb = b * b, ab = a * b, nv = sp.NG * N * sp.NR;
-  double *pt = at(sp.off_pend), *pz = pt + nv, *qt = pz + nv, *qx = qt + nv;
+  double *t = at(sp.off_t), *z = at(sp.off_z);
+  using Bits = unsigned long long;
   int* ctl = reinterpret_cast<int*>(w + sp.off_zero);
   int* flags = ctl + 8 * sp.nchunks;
   const int nr = (int)nrhs;
   auto ok = [&]() { return hipGetLastError(); };
   auto blocks = [](int64_t count) { return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (count + 255) / 256))); };
 
-  hipLaunchKernelGGL(solve_gather_kernel, blocks(sp.npend), dim3(256), 0, stream, rhs, nrhs, N, sp.NR, sp.NG, y,
-                     reinterpret_cast<unsigned long long*>(pt), sp.npend, ctl, sp.nzero);
+  hipLaunchKernelGGL(solve_gather_kernel, blocks(nv), dim3(256), 0, stream, rhs, nrhs, N, sp.NR, sp.NG, y,
+                     reinterpret_cast<Bits*>(t), reinterpret_cast<Bits*>(z), sp.npend, ctl, sp.nzero);
   if (hipError_t e = ok()) return e;
 
   auto invert_chunk = [&](int64_t i0, int64_t cnt) -> hipError_t {
@@ -745,12 +757,12 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
   };
   // one sweep over a chunk: enough workgroups for two phases in flight (the
   // second has its matrix elements loaded when the first ends), at most one a CU
-  auto chain = [&](bool bwd, int64_t c, const double* in, double* t, double* z) -> hipError_t {
+  auto chain = [&](bool bwd, int64_t c) -> hipError_t {
     ChainArgs p{};
-    p.LB = LB; p.W = W; p.y = in; p.t = t; p.z = z;
+    p.LB = LB; p.W = W; p.y = bwd ? z : y; p.t = t; p.z = bwd ? y : z;
     p.flags = flags + (bwd ? 2 * n * sp.NG * sp.S : 0);
     p.ctl = ctl + 4 * (2 * c + (bwd ? 1 : 0));
-    p.n = n; p.b = b; p.N = N; p.i0 = c * sp.C; p.i1 = std::min(n, p.i0 + sp.C);
+    p.n = n; p.b = b; p.N = N; p.Nt = sp.Nt; p.i0 = c * sp.C; p.i1 = std::min(n, p.i0 + sp.C);
     p.S = sp.S; p.NG = (int)sp.NG;
     p.ntasks = 2 * (p.i1 - p.i0) * sp.NG * sp.S;
     const long long grid = std::min<long long>(std::max(1, device_cu_count()), 2 * sp.NG * sp.S);
@@ -762,7 +774,7 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
 
   for (int64_t c = 0; c < sp.nchunks; ++c) {
     BTA_TRY_E(invert_chunk(c * sp.C, std::min<int64_t>(sp.C, n - c * sp.C)));
-    BTA_TRY_E(chain(false, c, y, pt, pz));
+    BTA_TRY_E(chain(false, c));
   }
 
   // ---- the tip: z_n = W_T (y_n - sum_i L_{n,i} z_i), x_n = W_T^T z_n, then
@@ -771,13 +783,13 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
     if (sp.NR == 1) {
       MvArgs pp{};
       pp.M = LR; pp.ld = b; pp.sMz = ab;
-      pp.x = pz; pp.sxy = N; pp.sxz = b;
+      pp.x = z; pp.sxy = N; pp.sxz = b;
       pp.out = ptip; pp.soy = n * a; pp.soz = a;
       pp.rows = a; pp.K = b; pp.tri = 0; pp.sign = 1.0;
       BTA_TRY_E(matvec_rows(pp, nr, (int)n, stream));
     } else {
-      hipLaunchKernelGGL(solve_tip16_kernel, dim3((unsigned)((a + TIP_ROWS - 1) / TIP_ROWS), (unsigned)n, (unsigned)sp.NG), dim3(256), 0, stream, LR, b, a,
-                         n, N, pz, ptip);
+      const dim3 g((unsigned)((a + TIP_ROWS - 1) / TIP_ROWS), (unsigned)n, (unsigned)sp.NG);
+      hipLaunchKernelGGL(solve_tip16_kernel, g, dim3(256), 0, stream, LR, b, a, n, N, z, ptip);
       if (hipError_t e = ok()) return e;
     }
     hipLaunchKernelGGL(solve_tip_rhs_kernel, dim3((unsigned)((a + 255) / 256), (unsigned)nrhs), dim3(256), 0, stream, y, N,
@@ -798,17 +810,20 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
     bx.out = xn; bx.soy = a;
     bx.rows = a; bx.K = a; bx.tri = 2; bx.sign = 1.0;
     BTA_TRY_E(matvec_rows(bx, nr, 1, stream));
+  }
+  if (a > 0 || sp.npend > 0) {
     dim3 g = blocks(n * b * sp.NR);
     g.y = (unsigned)sp.NG;
-    hipLaunchKernelGGL(solve_arrow_terms_kernel, g, dim3(256), 0, stream, LR, n, b, a, xn, nrhs, N, sp.NR, pz);
+    hipLaunchKernelGGL(solve_arrow_terms_kernel, g, dim3(256), 0, stream, LR, n, b, a, xn, nrhs, N, sp.NR, z,
+                       sp.npend ? reinterpret_cast<Bits*>(t) : nullptr, sp.npend ? reinterpret_cast<Bits*>(y) : nullptr);
     if (hipError_t e = ok()) return e;
   }
 
   for (int64_t c = sp.nchunks - 1; c >= 0; --c) {
     if (c < sp.nchunks - 1) BTA_TRY_E(invert_chunk(c * sp.C, sp.C));
-    BTA_TRY_E(chain(true, c, pz, qt, qx));
+    BTA_TRY_E(chain(true, c));
   }
-  hipLaunchKernelGGL(solve_scatter_kernel, blocks(N * nrhs), dim3(256), 0, stream, rhs, nrhs, N, n * b, sp.NR, qx, xn);
+  hipLaunchKernelGGL(solve_scatter_kernel, blocks(N * nrhs), dim3(256), 0, stream, rhs, nrhs, N, n * b, sp.NR, y, xn);
   return ok();
 }
 

@@ -161,3 +161,14 @@ def test_solve_group_width(L, n, b, nrhs, group):
     """Right-hand sides per group of the solve, on both sides of its rule."""
     L.bta_internal_solve_group.argtypes = [ctypes.c_int64] * 4
     assert L.bta_internal_solve_group(n, b, 4, nrhs) == group
+
+
+@pytest.mark.parametrize("n,b,a,nrhs", [(4096, 512, 4, 64), (512, 1024, 4, 1024), (128, 2048, 8, 16), (100000, 64, 2, 256)])
+def test_solve_workspace_holds_one_copy(L, n, b, a, nrhs):
+    """Many right-hand sides: the inverses' 2 GiB and the vectors once (with one
+    block's work vectors, the tip's and the flags), not once per sweep and phase."""
+    L.bta_workspace_bytes.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 4
+    L.bta_workspace_bytes.restype = ctypes.c_size_t
+    N = n * b + a
+    small = 8 * nrhs * (b + a * (n + 3)) + 4 * n * (nrhs // 16) * (b // 16) * 4 + 16 * a * a + (1 << 20)
+    assert L.bta_workspace_bytes(2, n, b, a, nrhs) <= (2 << 30) + 8 * N * nrhs + small
