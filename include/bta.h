@@ -19,8 +19,9 @@
  * Common conventions:
  *  - Every pointer argument is a device pointer (HIP device memory of the
  *    current device) owned by the caller; the library never allocates or
- *    frees memory.  Scratch memory is the caller's `work` buffer of at least
- *    bta_workspace_bytes(op, ...) bytes, 256-byte aligned.
+ *    frees memory.  Scratch memory is the caller's `work` buffer of
+ *    bta_workspace_bytes(op, ...) bytes or more (bta_workspace_min_bytes at
+ *    least), 256-byte aligned.
  *  - Every call only validates its arguments and enqueues work on `stream`
  *    (0 = the null stream); it returns before the work runs (one exception:
  *    the first bta_selinv_batched call with a descriptor set).  The return
@@ -77,6 +78,13 @@ typedef enum {
  * BTA_OP_SOLVE only).  Returns 0 for invalid sizes. */
 BTA_API size_t bta_workspace_bytes(int op, int64_t n, int64_t b, int64_t a, int64_t nrhs);
 
+/* The least workspace that `op` accepts: bta_workspace_bytes, except that
+ * bta_selinv of small blocks (b <= 1280, odd b <= 1088) also runs without the
+ * 8 (n-1) b^2 bytes, at most 8 GiB, that hold the products L_{i+1,i} L_ii^{-1}
+ * of all blocks for its persistent backward sweep.  It then sweeps product by
+ * product (b = 512: about twice the time). */
+BTA_API size_t bta_workspace_min_bytes(int op, int64_t n, int64_t b, int64_t a, int64_t nrhs);
+
 /*
  * POBTAF (Algorithm 1): block Cholesky factorization A = L L^T.
  *  in : D, B, R, T   blocks of A (lower triangles of D[i] and T are read)
@@ -122,6 +130,8 @@ BTA_API bta_status bta_factor_noalloc(int64_t n, int64_t b, int64_t a,
  *  out: XD, XB, XR, XT   blocks of Sigma = A^{-1} at the BTA pattern:
  *       Sigma_{i,i} and Sigma_{n,n} full symmetric, Sigma_{i+1,i},
  *       Sigma_{n,i}.
+ * Workspace: bta_workspace_bytes(BTA_OP_SELINV, n, b, a, 0), or less down to
+ * bta_workspace_min_bytes.
  */
 BTA_API bta_status bta_selinv(int64_t n, int64_t b, int64_t a,
                const double* LD, const double* LB, const double* LR, const double* LT,

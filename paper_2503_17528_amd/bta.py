@@ -25,7 +25,7 @@ BTA_OK, BTA_EINVAL, BTA_EHIP, BTA_ENOTSUP = 0, 1, 3, 4
 NOT_POSITIVE_DEFINITE = 2
 BTA_OP_FACTOR, BTA_OP_SELINV, BTA_OP_SOLVE, BTA_OP_LOGDET = 0, 1, 2, 3
 
-EXPORTED = ("bta_workspace_bytes", "bta_factor", "bta_factor_noalloc", "bta_selinv", "bta_solve", "bta_logdet",
+EXPORTED = ("bta_workspace_bytes", "bta_workspace_min_bytes", "bta_factor", "bta_factor_noalloc", "bta_selinv", "bta_solve", "bta_logdet",
             "bta_logdet_quad", "bta_grad_logdet_quad", "bta_batched_workspace_bytes", "bta_factor_batched",
             "bta_selinv_batched", "bta_status_string", "bta_last_error")
 
@@ -61,6 +61,8 @@ def lib() -> ctypes.CDLL:
     i64, vp, sz = ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
     L.bta_workspace_bytes.argtypes = [ctypes.c_int, i64, i64, i64, i64]
     L.bta_workspace_bytes.restype = sz
+    L.bta_workspace_min_bytes.argtypes = [ctypes.c_int, i64, i64, i64, i64]
+    L.bta_workspace_min_bytes.restype = sz
     L.bta_factor.argtypes = [i64, i64, i64] + [vp] * 8 + [vp, sz, vp, vp]
     L.bta_factor.restype = ctypes.c_int
     L.bta_factor_noalloc.argtypes = [i64, i64, i64] + [vp] * 8 + [vp, vp]
@@ -104,6 +106,10 @@ def gemm_mode(mode: int = -1) -> int:
 
 def bta_workspace_bytes(op: int, n: int, b: int, a: int, nrhs: int = 0) -> int:
     return int(lib().bta_workspace_bytes(op, n, b, a, nrhs))
+
+
+def bta_workspace_min_bytes(op: int, n: int, b: int, a: int, nrhs: int = 0) -> int:
+    return int(lib().bta_workspace_min_bytes(op, n, b, a, nrhs))
 
 
 def bta_factor(n, b, a, D, B, R, T, LD, LB, LR, LT, work, work_bytes, d_info, stream) -> int:
@@ -192,10 +198,18 @@ def _validate(t, shape, name):
 
 
 def workspace(op: int, n: int, b: int, a: int, device, nrhs: int = 0):
+    """A workspace tensor for ``op`` and its bytes; the least one that the call
+    accepts where the device has no room for more."""
     import torch
 
     nbytes = bta_workspace_bytes(op, n, b, a, nrhs)
-    return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device), nbytes
+    try:
+        return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device), nbytes
+    except torch.OutOfMemoryError:
+        least = bta_workspace_min_bytes(op, n, b, a, nrhs)
+        if least == nbytes:
+            raise
+    return torch.empty(max(least, 1), dtype=torch.uint8, device=device), least
 
 
 def factor(D, B, R, T, out=None, work=None, stream=None, check: bool = True):

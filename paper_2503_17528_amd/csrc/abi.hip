@@ -153,6 +153,11 @@ size_t bta_workspace_bytes(int op, int64_t n, int64_t b, int64_t a, int64_t nrhs
   }
 }
 
+size_t bta_workspace_min_bytes(int op, int64_t n, int64_t b, int64_t a, int64_t nrhs) {
+  if (op == BTA_OP_SELINV && dims_ok(n, b, a)) return bta::selinv_min_bytes(n, b, a);
+  return bta_workspace_bytes(op, n, b, a, nrhs);
+}
+
 bta_status bta_factor(int64_t n, int64_t b, int64_t a, const double* D, const double* B, const double* R, const double* T,
                double* LD, double* LB, double* LR, double* LT, void* work, size_t work_bytes, int64_t* d_info,
                bta_stream_t stream) {
@@ -198,7 +203,9 @@ bta_status bta_selinv(int64_t n, int64_t b, int64_t a, const double* LD, const d
   const int pair[8] = {4, 5, 6, 7, 0, 1, 2, 3};
   bta_status st = check_arrays(arr, 8, pair);
   if (st) return st;
-  const bta::SelinvPlan sp = bta::selinv_plan(n, b, a);
+  st = check_work(work, work_bytes, bta::selinv_min_bytes(n, b, a));
+  if (st) return st;
+  const bta::SelinvPlan sp = bta::selinv_plan_within(n, b, a, work_bytes);
   st = check_work(work, work_bytes, sp.bytes);
   if (st) return st;
   st = device_ok();

@@ -118,7 +118,13 @@ hipError_t sweep_launch(int64_t n, int64_t b, int64_t a, const double* PB, const
                         double* XB, double* XR, void* work, hipStream_t stream);
 // split: reserve the split-k partials of the sweep products (single-matrix
 // calls; the batched selected inversion has parallelism across matrices).
-SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split = true);
+// sweep: the persistent sweep where its rule allows it, which needs room for
+// every P_B; false: product by product.
+SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split = true, bool sweep = true);
+// The plan of a call with this much workspace (the persistent sweep if it fits),
+// and the least workspace that any plan takes.
+SelinvPlan selinv_plan_within(int64_t n, int64_t b, int64_t a, size_t work_bytes);
+size_t selinv_min_bytes(int64_t n, int64_t b, int64_t a);
 hipError_t selinv_launch(const SelinvPlan& sp, int64_t n, int64_t b, int64_t a,
                          const double* LD, const double* LB, const double* LR, const double* LT,
                          double* XD, double* XB, double* XR, double* XT,

@@ -183,7 +183,7 @@ static int selinv_split_max(int64_t b, int64_t a) {
 // loads, 641 126 / 101, 1025 295 / 288.
 static int64_t sweep_max_b(int64_t b) { return b % 2 == 0 ? 1280 : 1088; }
 
-SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
+SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split, bool sweep) {
   SelinvPlan sp{};
   const int64_t T = (b + 63) / 64;
   // enough blocks per chunk to give the 64-tile inverses ~512 workgroups,
@@ -205,7 +205,7 @@ SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
   // One persistent launch for the sweep where its products are too small for
   // launches of their own, within 8 GiB for all P_B (they then have a place of
   // their own, as the sweep writes X_{i+1,i} while others still read P_B).
-  sp.sweep = split && n > 1 && b <= sweep_max_b(b) && (n - 1) * b * b <= (int64_t(8) << 30) / 8;
+  sp.sweep = sweep && split && n > 1 && b <= sweep_max_b(b) && (n - 1) * b * b <= (int64_t(8) << 30) / 8;
   sp.off_PB = take(sp.sweep ? 8 * bb * (size_t)(n - 1) : 8);
   sp.off_sweep = take(sp.sweep ? sweep_work_bytes(n, b, a) : 8);
   // split-k partial products of the sweep at small b (few output tiles)
@@ -214,6 +214,17 @@ SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split) {
   sp.off_split = take(8 * std::max<size_t>(1, sp.split_doubles));
   sp.bytes = off;
   return sp;
+}
+
+// The sweep's plan is the larger one from a few blocks on (all P_B against one
+// block's split-k partials).
+SelinvPlan selinv_plan_within(int64_t n, int64_t b, int64_t a, size_t work_bytes) {
+  const SelinvPlan sp = selinv_plan(n, b, a);
+  return sp.sweep && work_bytes < sp.bytes ? selinv_plan(n, b, a, true, false) : sp;
+}
+
+size_t selinv_min_bytes(int64_t n, int64_t b, int64_t a) {
+  return std::min(selinv_plan(n, b, a).bytes, selinv_plan(n, b, a, true, false).bytes);
 }
 
 // Preprocessing chunks [i0, i1), from the last block down: the first ones
@@ -441,8 +452,8 @@ static bool windows_meet(const Window& x, const Window& y) {
 // also reads through another window (identical windows are the epilogue's
 // read-then-write of its own C tile).  In place (outputs = inputs) the same
 // checks run with the bounds of the shared arrays.  Returns 0 when all hold.
-static int selinv_dry_run(int64_t n, int64_t b, int64_t a, bool inplace) {
-  const SelinvPlan sp = selinv_plan(n, b, a);
+static int selinv_dry_run(int64_t n, int64_t b, int64_t a, bool inplace, bool sweep) {
+  const SelinvPlan sp = selinv_plan(n, b, a, true, sweep);
   const uintptr_t G = uintptr_t(1) << 40;
   const size_t sz[9] = {(size_t)(n * b * b) * 8, (size_t)((n - 1) * b * b) * 8, (size_t)(n * a * b) * 8, (size_t)(a * a) * 8,
                         (size_t)(n * b * b) * 8, (size_t)((n - 1) * b * b) * 8, (size_t)(n * a * b) * 8, (size_t)(a * a) * 8,
@@ -480,10 +491,13 @@ static int selinv_dry_run(int64_t n, int64_t b, int64_t a, bool inplace) {
 }
 
 int selinv_dry_check(int64_t n, int64_t b, int64_t a) {
-  const int r = selinv_dry_run(n, b, a, false);
-  if (r) return r;
-  const int q = selinv_dry_run(n, b, a, true);
-  return q ? 10 + q : 0;
+  for (const bool sweep : {true, false}) {
+    const int r = selinv_dry_run(n, b, a, false, sweep);
+    if (r) return r;
+    const int q = selinv_dry_run(n, b, a, true, sweep);
+    if (q) return 10 + q;
+  }
+  return 0;
 }
 
 }  // namespace bta

@@ -51,6 +51,26 @@ def test_workspace_bytes(bta):
     assert bta.bta_workspace_bytes(0, 8, 256, 4, 0) > bta.bta_workspace_bytes(0, 4, 256, 4, 0)
 
 
+@pytest.mark.parametrize("n,b,a", [(1, 64, 4), (2, 64, 4), (3, 1, 0), (16, 64, 4), (256, 512, 4), (64, 1024, 256), (9, 1087, 3),
+                                   (9, 1089, 3), (24, 2865, 4)])
+def test_least_workspace(bta, n, b, a):
+    """The selected inversion of small blocks also takes a workspace without room
+    for the products of all blocks; every other call needs what it asks for."""
+    for op in (bta.BTA_OP_FACTOR, bta.BTA_OP_SOLVE, bta.BTA_OP_LOGDET):
+        assert bta.bta_workspace_min_bytes(op, n, b, a, 7) == bta.bta_workspace_bytes(op, n, b, a, 7)
+    full, least = (f(bta.BTA_OP_SELINV, n, b, a, 0) for f in (bta.bta_workspace_bytes, bta.bta_workspace_min_bytes))
+    assert 0 < least <= full
+    limit = 1280 if b % 2 == 0 else 1088
+    if n > 8 and b <= limit:  # at most one block's split-k partials (four) in their place
+        assert full - least >= 8 * (n - 1 - 4) * b * b
+    elif b > limit:
+        assert full == least
+    assert bta.bta_workspace_min_bytes(bta.BTA_OP_SELINV, 0, b, a, 0) == 0
+    X = [1 << 40, 2 << 40, 3 << 40, 4 << 40] * 2  # (in place; never touched: the size is refused first)
+    st = bta.bta_selinv(n, b, a, *X, 5 << 40, least - 1, None)
+    assert st == bta.BTA_EINVAL and "workspace too small" in bta.bta_last_error()
+
+
 def test_status_strings(bta):
     for st in (bta.BTA_OK, bta.BTA_EINVAL, bta.BTA_EHIP, bta.BTA_ENOTSUP):
         assert bta.bta_status_string(st).startswith("BTA_")

@@ -97,6 +97,60 @@ def test_sweep_tiles(torch_cuda, n, b, a):
         assert torch_cuda.equal(x, y)
 
 
+# blocks that the persistent sweep takes (ragged, odd, split-k, wide tips), the first sizes it does not, one block
+@pytest.mark.parametrize("n,b,a", [(7, 33, 2), (7, 130, 70), (8, 520, 4), (6, 641, 3), (6, 768, 130), (6, 1024, 0), (6, 1087, 2),
+                                   (3, 1089, 3), (3, 1282, 4), (1, 1500, 4), (1, 512, 700)])
+def test_selinv_product_by_product(torch_cuda, n, b, a):
+    """The selected inversion with the least workspace (the sweep product by
+    product on several streams), out of place, twice, and in place: against the
+    oracle, and the same bits each time."""
+    from paper_2503_17528_amd import bta
+
+    say(f"case selinv least workspace n={n} b={b} a={a}")
+    wl = synth.workload(n, b, a, "literal" if b <= 512 else "scaled")
+    Q = synth.make_np(wl, 6)
+    F = oracle.pobtaf(Q["D"], Q["B"], Q["R"], Q["T"])
+    Xo = oracle.pobtasi(F["LD"], F["LB"], F["LR"], F["LT"])
+    L = to_dev({k: F["L" + k] for k in "DBRT"})
+    work = torch_cuda.empty(bta.bta_workspace_min_bytes(bta.BTA_OP_SELINV, n, b, a), dtype=torch_cuda.uint8, device="cuda")
+    X = bta.selinv(*L, work=work)
+    Y = bta.selinv(*L, work=work)
+    Z = bta.selinv(*L, out=L, work=work)
+    for x, y, z in zip(X, Y, Z):
+        assert torch_cuda.equal(x, y) and torch_cuda.equal(x, z)
+    e = errs(dict(zip("DBRT", to_np(X))), {"D": Xo["XD"], "B": Xo["XB"], "R": Xo["XR"], "T": Xo["XT"]}, lower=())
+    say(f"   X err {e}")
+    assert max(e.values()) < TOL
+
+
+def test_workspace_falls_back_to_the_least(torch_cuda):
+    """No room for the workspace that the selected inversion asks for: the binding
+    takes the least one, and the result is the product-by-product one."""
+    from paper_2503_17528_amd import bta
+
+    torch, n, b, a = torch_cuda, 200, 256, 4
+    say(f"case workspace fallback n={n} b={b} a={a}")
+    L = bta.factor(*to_dev(synth.make_np(synth.workload(n, b, a), 2)))[:4]
+    full, least = (f(bta.BTA_OP_SELINV, n, b, a) for f in (bta.bta_workspace_bytes, bta.bta_workspace_min_bytes))
+    out = [torch.empty_like(t) for t in L]
+    want = bta.selinv(*L, work=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (full + least) // 2) / total)
+    try:
+        work, nbytes = bta.workspace(bta.BTA_OP_SELINV, n, b, a, "cuda")
+        assert nbytes == work.numel() == least
+        del work
+        bta.selinv(*L, out=out)
+        with pytest.raises(torch.OutOfMemoryError):  # nothing smaller to fall back to
+            bta.workspace(bta.BTA_OP_SOLVE, 4000, b, a, "cuda", 64)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    for x, y in zip(out, want):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("n,b,a", [(3, 384, 6), (2, 520, 8), (4, 136, 2), (2, 64, 130), (5, 192, 0)])
 def test_selinv_gemm_kernels(torch_cuda, n, b, a, mode):
