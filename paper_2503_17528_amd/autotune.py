@@ -11,7 +11,9 @@ The library keeps its tuned decisions in a table keyed by
 - its k-loop load path (``cached``: 1 reads published operand tiles through
   the L2);
 - the largest split count of the selected inversion's sweep products at
-  small b (op ``selinv``, knob ``split``);
+  small b (op ``selinv``, knob ``split``), where the sweep runs product by
+  product: in a workspace too small for the persistent sweep, or where its
+  products L_{i+1,i} L_ii^{-1} exceed 8 GiB;
 - the batched selected inversion's tile shape per merged stage class
   (``tile128``, measured by the library itself on first use).
 
@@ -67,6 +69,8 @@ def _lib():
     L.bta_internal_factor_lookahead.restype = ctypes.c_int
     L.bta_internal_factor_cached_loads.argtypes = [ctypes.c_int]
     L.bta_internal_factor_cached_loads.restype = ctypes.c_int
+    L.bta_internal_selinv_splits.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    L.bta_internal_selinv_splits.restype = ctypes.c_int
     return L
 
 
@@ -181,24 +185,28 @@ def tune_factor(n: int, b: int, a: int, looks: Iterable[int] = (2, 4, 6, 8, 12, 
 
 def tune_selinv_split(n: int, b: int, a: int, splits: Iterable[int] = (1, 2, 3, 4), reps: int = 3, seed: int = 0,
                       log=None) -> Dict[str, float]:
-    """Time bta_selinv on the factor of a seeded n x (b, a) matrix for every
-    largest split count of the sweep products (``split``: 1 = no split; the
-    library splits only where a product's 64 x 64 tiles fill under half the
-    CUs), the median of ``reps`` runs each, and record the fastest as the
-    table's ``split`` entry for (b, a).  ``BTA_SELINV_SPLIT``, when set,
-    overrides the table and makes the candidates equal.
-    Returns {"split=<s>": median ms}."""
+    """Time bta_selinv, with the sweep product by product (the least workspace),
+    on the factor of a seeded n x (b, a) matrix for every largest split count of
+    the sweep products (``split``: 1 = no split; the library splits only where a
+    product's 64 x 64 tiles fill under half the CUs), the median of ``reps`` runs
+    each, and record the fastest as the table's ``split`` entry for (b, a).  Block
+    sizes whose products are never split are not timed and get no entry.
+    ``BTA_SELINV_SPLIT``, when set, overrides the table and makes the candidates
+    equal.  Returns {"split=<s>": median ms}, empty where nothing was timed."""
     import torch
 
     if reps < 3:
         raise ValueError("reps >= 3 (the median of at least three runs)")
+    if _lib().bta_internal_selinv_splits(b, a, 4) < 2:
+        return {}
+    n = max(n, 6)  # with fewer blocks the persistent sweep takes no more workspace than the products
     reading = "scaled" if b >= 2048 else "literal"
     wl = synth.workload(n, b, a, reading)
     dev = torch.device("cuda", torch.cuda.current_device())
     Q = synth.make_torch(wl, seed, dev)
     L = bta.factor(Q["D"], Q["B"], Q["R"], Q["T"])[:4]
     out = tuple(torch.empty_like(t) for t in L)
-    work, _ = bta.workspace(bta.BTA_OP_SELINV, n, b, a, dev)
+    work = torch.empty(bta.bta_workspace_min_bytes(bta.BTA_OP_SELINV, n, b, a), dtype=torch.uint8, device=dev)
     k = key("selinv", b, a, "split")
     prev = get_entry(k)
     times: Dict[str, float] = {}

@@ -99,6 +99,10 @@ BTA_TESTING_API int bta_internal_tune_clear(void);
  * every tile is produced once and every wait is for a smaller ticket. */
 BTA_TESTING_API int bta_internal_sweep_check(int64_t n, int64_t b, int64_t a);
 
+/* Largest split count (1: none) of the products of the sweep product by product,
+ * of at most smax splits (0: the setting in force) (selinv.hip). */
+BTA_TESTING_API int bta_internal_selinv_splits(int64_t b, int64_t a, int smax);
+
 /* Right-hand sides per group of a solve, 1 or 16 (solve.hip). */
 BTA_TESTING_API int bta_internal_solve_group(int64_t n, int64_t b, int64_t a, int64_t nrhs);
 

@@ -505,3 +505,24 @@ int selinv_dry_check(int64_t n, int64_t b, int64_t a) {
 BTA_TESTING_API int bta_internal_selinv_dry_check(int64_t n, int64_t b, int64_t a) {
   return bta::selinv_dry_check(n, b, a);
 }
+
+// Largest split count of the product-by-product sweep's two products, with at
+// most smax splits (0: the current setting); 1 where no product is split.
+BTA_TESTING_API int bta_internal_selinv_splits(int64_t b, int64_t a, int smax) {
+  using namespace bta;
+  const SelinvPlan sp = selinv_plan(2, b, a, true, false);
+  DryRecorder rec;
+  DryRecorder* const prev = g_dry;
+  g_dry = &rec;  // (without a device: plan for the full chip)
+  int most = 1;
+  for (const int lower : {0, 1}) {
+    GProb p = prob_init();
+    p.seg[0] = seg(nullptr, b, lower, nullptr, b, 1, (int)b, TRI_NONE);
+    p.nseg = 1;
+    p.M = (int)b; p.N = (int)b;
+    p.lower_tiles = lower;
+    most = std::max(most, splitk_factor(p, sp.split_doubles, smax > 0 ? smax : sp.split_max));
+  }
+  g_dry = prev;
+  return most;
+}

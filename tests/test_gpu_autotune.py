@@ -87,3 +87,36 @@ def _run(torch, autotune, bta, tmp_path):
     autotune.clear()
     autotune.load(path)
     assert autotune.table() == tab
+
+
+def test_split_tuner_times_split_products():
+    """The split tuner times the sweep it tunes: with the workspace that it uses
+    the split counts give different sums, and the recorded one is in force; block
+    sizes whose products are never split are not timed and get no entry."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2503_17528_amd import autotune, bta
+
+    lib, n, b, a = autotune._lib(), 6, 512, 4
+    try:
+        for bb in (64, 200, 1100, 1500):
+            say(f"case split tuner b={bb}: not split")
+            assert autotune.tune_selinv_split(3, bb, 2) == {}
+            assert autotune.get_entry(autotune.key("selinv", bb, 2, "split")) is None
+        say(f"case split tuner b={b}")
+        assert lib.bta_internal_selinv_splits(b, a, 4) >= 2
+        Q = synth.make_torch(synth.workload(n, b, a), 4, "cuda")
+        L = bta.factor(Q["D"], Q["B"], Q["R"], Q["T"])[:4]
+        work = torch.empty(bta.bta_workspace_min_bytes(bta.BTA_OP_SELINV, n, b, a), dtype=torch.uint8, device="cuda")
+        X = {}
+        for sp in (1, 4):
+            autotune.set_entry(autotune.key("selinv", b, a, "split"), sp)
+            assert lib.bta_internal_selinv_splits(b, a, 0) == sp
+            X[sp] = bta.selinv(*L, work=work)
+        assert not torch.equal(X[1][0], X[4][0])
+        st = autotune.tune_selinv_split(2, b, a)
+        sp = autotune.get_entry(autotune.key("selinv", b, a, "split"))
+        assert f"split={sp}" == min(st, key=st.get) and lib.bta_internal_selinv_splits(b, a, 0) == sp
+    finally:
+        autotune.clear()
