@@ -98,9 +98,9 @@ def lib() -> ctypes.CDLL:
 
 
 def gemm_mode(mode: int = -1) -> int:
-    """Select the GEMM kernels of the selected inversion (0 automatic,
-    1 4-byte operand loads, 2 16-byte ones where the operands allow, 3, 5
-    64 x 64 tiles, 4, 6, 7 128 x 128 tiles);
+    """Select the GEMM kernels of the selected inversion: 0 automatic,
+    1 4-byte operand loads, 2 16-byte ones where the operands allow; with 64 x 64
+    and 128 x 128 tiles: 3 and 4 as 2, 5 and 6 as 1, 7 as 4 with two LDS stages.
     -1 only queries.  Returns the previous mode."""
     return int(lib().bta_internal_gemm_mode(int(mode)))
 

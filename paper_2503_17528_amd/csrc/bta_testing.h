@@ -107,10 +107,13 @@ BTA_TESTING_API int bta_internal_selinv_splits(int64_t b, int64_t a, int smax);
 BTA_TESTING_API int bta_internal_solve_group(int64_t n, int64_t b, int64_t a, int64_t nrhs);
 
 /* ---- GEMM engine and measurement (gemm.hip) */
-/* GEMM kernel family of the selected inversion (0 automatic, 1 4-byte operand
- * loads, 2 16-byte ones where allowed, 3, 5 64 x 64 and 4, 6, 7 128 x 128 tiles); returns the
- * previous mode (-1 only queries). */
+/* GEMM kernels of the selected inversion: 0 automatic, 1 4-byte operand loads, 2
+ * 16-byte ones where allowed; with 64 x 64 and 128 x 128 tiles: 3 and 4 as 2, 5 and 6
+ * as 1, 7 as 4 with two LDS stages.  Returns the previous mode (-1 only queries). */
 BTA_TESTING_API int bta_internal_gemm_mode(int mode);
+/* The calling thread's last product launch: tile edge (64 or 128), + 1 for 4-byte
+ * operand loads, + 2 for two LDS stages of a 128 x 128 tile. */
+BTA_TESTING_API int bta_internal_gemm_kind(void);
 /* One product through the grouped GEMM: C = beta*Cin + alpha*sum_k A(m,k) B(c,k). */
 BTA_TESTING_API int bta_internal_gemm(int M, int N, int K, const double* A, int64_t lda, int at, const double* B,
                                       int64_t ldb, int bt, int tri, const double* Cin, double* C, int64_t ldc,

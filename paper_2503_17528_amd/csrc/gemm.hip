@@ -574,10 +574,13 @@ static long long plan_tiles(GemmArgs& args, GProb* probs, int nprob, int TM, int
   return total;
 }
 
-// 0: choose per launch; 1: the 4-byte loads only; 2: the 16-byte loads
-// wherever the operands allow; 3, 5: 64 x 64 tiles; 4, 6, 7: 128 x 128 tiles
-// (tests run every path through this).
+// 0: choose per launch; 1: 4-byte loads; 2: 16-byte loads wherever the operands
+// allow; 3, 4: as 2, with 64 x 64, 128 x 128 tiles; 5, 6: as 1, with 64 x 64, 128 x
+// 128 tiles; 7: as 4, with two LDS stages (tests run every kernel through this).
 static int g_gemm_mode = 0;
+// The calling thread's last launch: tile edge, + 1 for 4-byte loads, + 2 for two
+// LDS stages of a 128 x 128 tile.
+static thread_local int g_gemm_kind = 0;
 
 // Sum over the tiles of a planned launch of the fraction of MFMA blocks a
 // tile computes (ragged edges and lower-store tiles compute fewer).
@@ -613,30 +616,31 @@ hipError_t gemm_launch(GProb* probs, int nprob, hipStream_t stream) {
       if (probs[i].M > 0 && probs[i].N > 0) record_gemm(probs[i]);
     return hipSuccess;
   }
-  bool dl = g_gemm_mode != 1;
+  const int mode = g_gemm_mode;
+  bool dl = mode != 1 && mode != 5 && mode != 6;
   for (int i = 0; i < nprob; ++i) dl = dl && dl_ok(probs[i]);
   GemmArgs big{}, small{};
   const long long t128 = plan_tiles(big, probs, nprob, 128, 128);
   const long long t64 = plan_tiles(small, probs, nprob, 64, 64);
   if (t64 == 0) return hipSuccess;
-  {
-    int kind = g_gemm_mode >= 3 ? g_gemm_mode : 0;
-    if (!dl || kind == 0) {
-      // 128 x 128 tiles (the most efficient per flop) when they fill the CUs
-      // in whole rounds (at least 3/4 of the last round) and are mostly full
-      // (ragged tiles cost nearly a whole tile of loads); otherwise 64 x 64
-      // tiles.
-      const double cus = std::max(1, device_cu_count());
-      const double rounds = std::ceil((double)t128 / cus);
-      const bool fill = (double)t128 >= 0.75 * rounds * cus;
-      const bool full = tile_weight(big, 128, 128) >= 0.85 * (double)t128;
-      kind = (fill && full) ? 7 : 5;
-      if (!dl) kind = kind == 7 ? 9 : 8;
-    }
-    // the first segment's layout when every problem of the launch shares it
-    int L0 = small.p[0].seg[0].at * 2 + small.p[0].seg[0].bt;
-    for (int i = 1; i < small.nprob; ++i)
-      if (small.p[i].seg[0].at * 2 + small.p[i].seg[0].bt != L0) L0 = 4;
+  bool wide = mode == 4 || mode >= 6;
+  if (mode < 3) {
+    // 128 x 128 tiles (the most efficient per flop) when they fill the CUs
+    // in whole rounds (at least 3/4 of the last round) and are mostly full
+    // (ragged tiles cost nearly a whole tile of loads); otherwise 64 x 64
+    // tiles.
+    const double cus = std::max(1, device_cu_count());
+    const double rounds = std::ceil((double)t128 / cus);
+    const bool fill = (double)t128 >= 0.75 * rounds * cus;
+    const bool full = tile_weight(big, 128, 128) >= 0.85 * (double)t128;
+    wide = fill && full;
+  }
+  const bool two = wide && dl && (mode == 7 || l128_stages() == 2);
+  g_gemm_kind = (wide ? 128 : 64) + (dl ? 0 : 1) + (two ? 2 : 0);
+  // the first segment's layout when every problem of the launch shares it
+  int L0 = small.p[0].seg[0].at * 2 + small.p[0].seg[0].bt;
+  for (int i = 1; i < small.nprob; ++i)
+    if (small.p[i].seg[0].at * 2 + small.p[i].seg[0].bt != L0) L0 = 4;
 #define BTA_LAUNCH_L0(KER, GRID, BLOCK, ARGS)                                                  \
   switch (L0) {                                                                                \
     case 0: hipLaunchKernelGGL((KER<0>), dim3((unsigned)(GRID)), dim3(BLOCK), 0, stream, ARGS); break; \
@@ -645,20 +649,15 @@ hipError_t gemm_launch(GProb* probs, int nprob, hipStream_t stream) {
     case 3: hipLaunchKernelGGL((KER<3>), dim3((unsigned)(GRID)), dim3(BLOCK), 0, stream, ARGS); break; \
     default: hipLaunchKernelGGL((KER<4>), dim3((unsigned)(GRID)), dim3(BLOCK), 0, stream, ARGS); break; \
   }
-    timing_mark(KT_GEMM, true, stream);
-    switch (kind) {
-      case 3: case 5: BTA_LAUNCH_L0(gemm_l64_kernel, t64, 256, small); break;
-      default:  // 4, 6, 7
-        if (l128_stages() == 2) BTA_LAUNCH_L0(gemm_l128s2_kernel, t128, 512, big)
-        else BTA_LAUNCH_L0(gemm_l128_kernel, t128, 512, big)
-        break;
-      case 8: BTA_LAUNCH_L0(gemm_u64_kernel, t64, 256, small); break;
-      case 9: BTA_LAUNCH_L0(gemm_u128_kernel, t128, 512, big); break;
-    }
+  timing_mark(KT_GEMM, true, stream);
+  if (!wide && dl) BTA_LAUNCH_L0(gemm_l64_kernel, t64, 256, small)
+  else if (!wide) BTA_LAUNCH_L0(gemm_u64_kernel, t64, 256, small)
+  else if (!dl) BTA_LAUNCH_L0(gemm_u128_kernel, t128, 512, big)
+  else if (two) BTA_LAUNCH_L0(gemm_l128s2_kernel, t128, 512, big)
+  else BTA_LAUNCH_L0(gemm_l128_kernel, t128, 512, big)
 #undef BTA_LAUNCH_L0
-    timing_mark(KT_GEMM, false, stream);
-    return hipGetLastError();
-  }
+  timing_mark(KT_GEMM, false, stream);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- split-k
@@ -916,6 +915,9 @@ BTA_TESTING_API int bta_internal_gemm_mode(int mode) {
   return prev;
 }
 
+// The calling thread's last gemm_launch (see g_gemm_kind).
+BTA_TESTING_API int bta_internal_gemm_kind(void) { return bta::g_gemm_kind; }
+
 // Internal: one product through the grouped GEMM (tests and measurements):
 // C = beta * Cin + alpha * sum_k A(m,k) B(c,k), operand layouts and k range as
 // in the selected inversion's problems.  Returns a HIP error code.
@@ -961,7 +963,7 @@ BTA_TESTING_API int bta_internal_gemm_skinny(int M, int N, int K, int K1, const 
 
 // A list of `nprob` copies of one product (problem q reads A + q*strideA,
 // B + q*strideB and writes C + q*strideC) through the 64 x 64 list kernel
-// (four LDS stages) or, with big, the 128 x 128 one; dlist is device memory of
+// or, with big, the 128 x 128 one; dlist is device memory of
 // at least 512 * (nprob + 1) bytes.  Returns the HIP status (synchronizes `s`).
 BTA_TESTING_API int bta_internal_gemm_list(int M, int N, int K, const double* A, int64_t lda, int at, const double* B,
                                            int64_t ldb, int bt, int tri, const double* Cin, double* C, int64_t ldc,

@@ -138,6 +138,33 @@ def test_gemm_operands_off_16_bytes(lib, M, N, K, at, bt):
     assert (np.abs(C.cpu().numpy() - prod) <= bound).all()
 
 
+# k loops of 1, 2, 3, 4 and many stages of 16, whole and with a remainder
+@pytest.mark.parametrize("mode,kind", [(3, 65), (4, 129), (5, 65), (6, 129)])
+@pytest.mark.parametrize("at,bt", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1, 129, 1), (63, 65, 16), (127, 129, 17), (129, 127, 32), (131, 191, 47), (257, 65, 48),
+                                   (65, 257, 63), (129, 129, 64), (191, 255, 65), (255, 193, 80), (257, 383, 257)])
+def test_gemm_kernels_off_16_bytes(lib, M, N, K, at, bt, mode, kind):
+    """The 4-byte loads in both tilings, by the launch that took them, whatever
+    the number of CUs: operands and bound of the test above."""
+    from paper_2503_17528_amd import bta
+
+    prev = bta.gemm_mode(mode)
+    try:
+        test_gemm_operands_off_16_bytes(lib, M, N, K, at, bt)
+        assert lib.bta_internal_gemm_kind() == kind
+    finally:
+        bta.gemm_mode(prev)
+
+
+@pytest.mark.parametrize("mode,kind", [(1, 65), (2, 64), (3, 64), (4, 128), (5, 65), (6, 129), (7, 130)])
+def test_gemm_mode_selects_kernel(lib, mode, kind):
+    """Each mode runs its own kernel on operands that take every load."""
+    from paper_2503_17528_amd import bta
+
+    test_gemm_kernels_match_reference(lib, (256, 256, 264, 1, 0, TRI_NONE, ST_LOWER, 1), mode)
+    assert lib.bta_internal_gemm_kind() == kind
+
+
 SPLIT_CASES = [
     # M, N, K, at, bt, store, lower_tiles, beta: the sweep's b x b product and its lower X_ii product
     (512, 512, 512, 0, 1, ST_FULL, 0, 0.0),
@@ -305,3 +332,14 @@ def test_gemm_list_kernels_match_reference(lib, case, big):
         worst = max(worst, err)
     say(f"   max rel err {worst:.2e}")
     assert worst < 1e-12
+
+
+# odd leading dimensions (every problem's operands take the 4-byte loads), several problems, k loops of five and
+# more stages in the four-stage pipeline of the 128 x 128 tiles
+@pytest.mark.parametrize("big", [0, 1])
+@pytest.mark.parametrize("case", [(129, 191, 65, 0, 1, TRI_NONE, ST_FULL, 0, 3), (255, 129, 131, 1, 0, TRI_NONE, ST_FULL, 0, 2),
+                                  (127, 127, 79, 0, 0, TRI_NONE, ST_FULL, 0, 4), (193, 193, 193, 0, 1, TRI_K_GE_COL, ST_FULL, 0, 2),
+                                  (255, 255, 255, 1, 1, TRI_K_GE_ROW, ST_LOWER_MIRROR, 1, 2)],
+                         ids=lambda c: "x".join(str(v) for v in c))
+def test_gemm_list_kernels_odd(lib, case, big):
+    test_gemm_list_kernels_match_reference(lib, case, big)
