@@ -132,6 +132,10 @@ BTA_API bta_status bta_factor_noalloc(int64_t n, int64_t b, int64_t a,
  *       Sigma_{n,i}.
  * Workspace: bta_workspace_bytes(BTA_OP_SELINV, n, b, a, 0), or less down to
  * bta_workspace_min_bytes.
+ * Where the backward sweep is one launch (see bta_workspace_min_bytes), its
+ * internal waits are bounded; if one gives up, after some seconds without
+ * progress, the entries that the sweep had not formed are NaN, some of Sigma_{0,0},
+ * which comes last, always among them.
  */
 BTA_API bta_status bta_selinv(int64_t n, int64_t b, int64_t a,
                const double* LD, const double* LB, const double* LR, const double* LT,
@@ -142,7 +146,9 @@ BTA_API bta_status bta_selinv(int64_t n, int64_t b, int64_t a,
  * Solve A x = rhs with the factor (block forward then back substitution; not
  * in the paper, which stops at the selected inverse: the textbook triangular
  * solves with L and L^T, needed for the objective of Gaussian models below).
- * rhs is [N][nrhs] row-major and is overwritten by x.
+ * rhs is [N][nrhs] row-major and is overwritten by x.  Internal waits are
+ * bounded; if one gives up, after some seconds without progress, every entry of x
+ * is NaN.
  * Workspace: bta_workspace_bytes(BTA_OP_SOLVE, n, b, a, nrhs).
  */
 BTA_API bta_status bta_solve(int64_t n, int64_t b, int64_t a,

@@ -283,6 +283,11 @@ inline void set_stage(int phase, int major, int minor) {
   }
   g_rec->key = StageKey{phase, major, minor};
 }
+// Polls after which a wait of the persistent sweeps (selected inversion, solve)
+// gives up: a few seconds without progress.  g_wait_limit: the calling thread's
+// limit (tests; the selected inversion takes 0 as waits that all have given up).
+constexpr long long WAIT_LIMIT = 1LL << 22;
+extern thread_local long long g_wait_limit;
 inline bool recording() { return g_dry != nullptr || g_rec != nullptr; }
 
 // problem-list GEMM launch (device-resident problem array and tile prefix);

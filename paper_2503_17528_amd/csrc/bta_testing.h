@@ -99,6 +99,11 @@ BTA_TESTING_API int bta_internal_tune_clear(void);
  * every tile is produced once and every wait is for a smaller ticket. */
 BTA_TESTING_API int bta_internal_sweep_check(int64_t n, int64_t b, int64_t a);
 
+/* Polls after which a wait of the calling thread's later bta_solve launches gives
+ * up; returns the previous limit (-1 only queries).  0: at the first poll that finds
+ * its data pending, and every wait of a bta_selinv that sweeps in one launch. */
+BTA_TESTING_API long long bta_internal_wait_limit(long long polls);
+
 /* Largest split count (1: none) of the products of the sweep product by product,
  * of at most smax splits (0: the setting in force) (selinv.hip). */
 BTA_TESTING_API int bta_internal_selinv_splits(int64_t b, int64_t a, int smax);

@@ -353,7 +353,7 @@ struct ChainArgs {
   int* ctl;                           // ticket counter (64 bits), abort flag at ctl[2]
   int64_t n, b, N, Nt, i0, i1;           // Nt: N, or b (groups of 16: one block's t)
   int S, NG;                          // tasks per phase and group, groups
-  long long ntasks;
+  long long ntasks, spin;             // spin: polls before a wait gives up (its outputs are then NaN)
 };
 
 struct ChainTask {
@@ -409,8 +409,6 @@ __device__ __forceinline__ double sum8(const double* p, int step) {
   return ((p[0] + p[step]) + (p[2 * step] + p[3 * step])) + ((p[4 * step] + p[5 * step]) + (p[6 * step] + p[7 * step]));
 }
 
-constexpr long long CHAIN_SPIN = 1LL << 22;  // polls before a wait gives up (its outputs are then NaN)
-
 __device__ __forceinline__ bool chain_aborted(const ChainArgs& p) {
   return __hip_atomic_load(p.ctl + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
@@ -459,7 +457,7 @@ __global__ __launch_bounds__(512, 2) void solve_chain_kernel(ChainArgs p) {
           v = ld_dev(x + kc + e);
           long long polls = 0;
           while (__builtin_bit_cast(unsigned long long, v) == SOLVE_PENDING) {
-            if (++polls > CHAIN_SPIN || ((polls & 63) == 0 && chain_aborted(p))) {
+            if (++polls > p.spin || ((polls & 63) == 0 && chain_aborted(p))) {
               __hip_atomic_store(p.ctl + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               break;
             }
@@ -551,7 +549,7 @@ __global__ __launch_bounds__(512, 2) void solve_chain16_kernel(ChainArgs p) {
           long long polls = 0;
           for (int e = f0 + lane; e < f1; e += 64)
             while (!flag_set(f + e)) {
-              if (++polls > CHAIN_SPIN || ((polls & 63) == 0 && chain_aborted(p))) {
+              if (++polls > p.spin || ((polls & 63) == 0 && chain_aborted(p))) {
                 __hip_atomic_store(p.ctl + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
               }
@@ -612,11 +610,17 @@ __global__ __launch_bounds__(256) void solve_gather_kernel(const double* rhs, in
   for (int64_t e = t0; e < npend; e += step) t[e] = z[e] = SOLVE_PENDING;
   for (int64_t e = t0; e < nzero; e += step) zero[e] = 0;
 }
+// x in the caller's layout; NaN throughout if a wait of any sweep gave up (part of
+// x may then be right, and nothing else would tell).
 __global__ __launch_bounds__(256) void solve_scatter_kernel(double* rhs, int64_t nrhs, int64_t N, int64_t nb, int NR,
-                                                            const double* x, const double* xn) {
+                                                            const double* x, const double* xn, const int* ctl,
+                                                            int64_t nsweeps) {
+  int gave_up = 0;
+  for (int64_t c = 0; c < nsweeps; ++c) gave_up |= ctl[4 * c + 2];
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < N * nrhs; e += (int64_t)gridDim.x * 256) {
     const int64_t r = e / nrhs, j = e - r * nrhs;
-    rhs[e] = r < nb ? x[rhs_at(j, r, N, NR)] : xn[j * (N - nb) + r - nb];
+    const double v = r < nb ? x[rhs_at(j, r, N, NR)] : xn[j * (N - nb) + r - nb];
+    rhs[e] = gave_up ? __builtin_nan("") : v;
   }
 }
 
@@ -765,6 +769,7 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
     p.n = n; p.b = b; p.N = N; p.Nt = sp.Nt; p.i0 = c * sp.C; p.i1 = std::min(n, p.i0 + sp.C);
     p.S = sp.S; p.NG = (int)sp.NG;
     p.ntasks = 2 * (p.i1 - p.i0) * sp.NG * sp.S;
+    p.spin = g_wait_limit;
     const long long grid = std::min<long long>(std::max(1, device_cu_count()), 2 * sp.NG * sp.S);
     auto kernel = sp.NR == 1 ? (bwd ? solve_chain_kernel<true> : solve_chain_kernel<false>)
                              : (bwd ? solve_chain16_kernel<true> : solve_chain16_kernel<false>);
@@ -823,7 +828,8 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
     if (c < sp.nchunks - 1) BTA_TRY_E(invert_chunk(c * sp.C, sp.C));
     BTA_TRY_E(chain(true, c));
   }
-  hipLaunchKernelGGL(solve_scatter_kernel, blocks(N * nrhs), dim3(256), 0, stream, rhs, nrhs, N, n * b, sp.NR, y, xn);
+  hipLaunchKernelGGL(solve_scatter_kernel, blocks(N * nrhs), dim3(256), 0, stream, rhs, nrhs, N, n * b, sp.NR, y, xn, ctl,
+                     2 * sp.nchunks);
   return ok();
 }
 

@@ -31,8 +31,6 @@ namespace bta {
 
 namespace {
 
-constexpr long long SWEEP_SPIN = 1LL << 22;  // polls before a wait gives up (its tile is then NaN)
-
 struct SweepArgs {
   const double* PB; const double* PR; const double* XT;
   double* XD; double* XB; double* XR;
@@ -98,12 +96,17 @@ __device__ __forceinline__ bool sweep_aborted(const SweepArgs& p) {
   return __hip_atomic_load(p.ctl + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
 
-// Lanes of one wave: wait for flag f0 + lane * step, lane < count.
+// Lanes of one wave: wait for flag f0 + lane * step, lane < count.  A wait that
+// gives up makes its own tile and those of every later wait NaN, so the last
+// block's tiles hold NaN after any of them.  (The limit is a constant and the tiles
+// that were done stay: the limit as an argument cost 0.5 and 1.6% at b = 512 and 640;
+// NaN for all of X cost 0.5% at b = 512 by the last workgroup, 1.5% at n = 16, b = 64
+// by a launch of its own.)
 __device__ __forceinline__ void sweep_wait(const SweepArgs& p, int64_t f0, int64_t step, int count, int lane) {
   long long polls = 0;
   for (int e = lane; e < count; e += 64)
     while (!flag_set(p.flags + f0 + e * step)) {
-      if (++polls > SWEEP_SPIN || ((polls & 63) == 0 && sweep_aborted(p))) {
+      if (++polls > WAIT_LIMIT || ((polls & 63) == 0 && sweep_aborted(p))) {
         __hip_atomic_store(p.ctl + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;
       }
@@ -266,8 +269,10 @@ __global__ __launch_bounds__(256, 1) void selinv_sweep_kernel(SweepArgs p) {
   }
 }
 
-__global__ __launch_bounds__(256) void sweep_reset_kernel(int* p, int64_t count) {
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256) p[e] = 0;
+// Control words and flags to zero; give_up: the abort flag set from the start.
+__global__ __launch_bounds__(256) void sweep_reset_kernel(int* p, int64_t count, int give_up) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256)
+    p[e] = e == 2 ? give_up : 0;
 }
 
 // Tile edge 64 from this b on: at 32 a phase reads its operands twice as often and,
@@ -315,7 +320,7 @@ hipError_t sweep_launch(int64_t n, int64_t b, int64_t a, const double* PB, const
   p.flags = p.ctl + 64;
   const int64_t ints = (int64_t)(sweep_work_bytes(n, b, a) / 4);
   hipLaunchKernelGGL(sweep_reset_kernel, dim3((unsigned)std::min<int64_t>(1024, (ints + 255) / 256)), dim3(256), 0, s, p.ctl,
-                     ints);
+                     ints, g_wait_limit == 0 ? 1 : 0);
   auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
   const bool pairs = b % 2 == 0 && a % 2 == 0 && al(PB) && al(PR) && al(XT) && al(XD) && al(XB) && al(XR);
   const long long grid = std::min<long long>(p.ntasks, std::max(1, device_cu_count()));
@@ -328,6 +333,16 @@ hipError_t sweep_launch(int64_t n, int64_t b, int64_t a, const double* PB, const
 }
 
 }  // namespace bta
+
+namespace bta {
+thread_local long long g_wait_limit = WAIT_LIMIT;
+}
+
+BTA_TESTING_API long long bta_internal_wait_limit(long long polls) {
+  const long long prev = bta::g_wait_limit;
+  if (polls >= 0) bta::g_wait_limit = polls;
+  return prev;
+}
 
 // Host replay of the sweep's tickets: every flag index in bounds and set once,
 // and every awaited flag set by a smaller ticket.  Returns 0 when all hold.

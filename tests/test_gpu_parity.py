@@ -4,6 +4,8 @@ Every block of L and of the selected inverse must match the oracle within
 1e-10 relative Frobenius error; strict upper triangles of the diagonal
 factor blocks must be exact zeros; symmetric outputs exactly symmetric.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -297,6 +299,34 @@ def test_solve_chunks(torch_cuda, nrhs):
     e = float((got - x).norm() / x.norm())
     say(f"   solve rel err {e:.3e}")
     assert e < TOL
+
+
+@pytest.mark.parametrize("n,b,a", [(6, 256, 4), (5, 193, 0), (4, 800, 70)])
+def test_wait_that_gives_up_leaves_nan(torch_cuda, n, b, a):
+    """Waits of the persistent sweeps that give up (in the solve the first to find
+    its data pending, in the selected inversion all): everything that depends on them
+    is NaN, all of x included, the call ends, and the next one is as good as any."""
+    from paper_2503_17528_amd import bta
+
+    torch = torch_cuda
+    say(f"case waits give up n={n} b={b} a={a}")
+    lib = bta.lib()
+    lib.bta_internal_wait_limit.argtypes = [ctypes.c_longlong]
+    lib.bta_internal_wait_limit.restype = ctypes.c_longlong
+    L = bta.factor(*to_dev(synth.make_np(synth.workload(n, b, a, "scaled"), 2)))[:4]
+    y = [torch.randn(n * b + a, k, dtype=torch.float64, device="cuda") for k in (1, 64)]
+    want = list(bta.selinv(*L)) + [bta.solve(*L, v) for v in y]
+    torch.cuda.synchronize()
+    prev = lib.bta_internal_wait_limit(0)
+    try:
+        void = list(bta.selinv(*L)) + [bta.solve(*L, v) for v in y]
+        torch.cuda.synchronize()
+    finally:
+        lib.bta_internal_wait_limit(prev)
+    assert all(bool(t.isnan().all()) for t in void[:3] + void[4:])
+    assert torch.equal(void[3], want[3])  # X_nn does not depend on the sweep
+    again = list(bta.selinv(*L)) + [bta.solve(*L, v) for v in y]
+    assert all(torch.equal(p, q) for p, q in zip(want, again))
 
 
 def test_abi_rejects_bad_workspace_on_device(torch_cuda):
