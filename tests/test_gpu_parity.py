@@ -125,6 +125,19 @@ def test_selinv_product_by_product(torch_cuda, n, b, a):
     assert max(e.values()) < TOL
 
 
+@pytest.mark.parametrize("mode", [1, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("n,b,a", [(7, 384, 6), (6, 193, 130)])
+def test_selinv_product_by_product_kernels(torch_cuda, n, b, a, mode):
+    """The same path with every product kernel."""
+    from paper_2503_17528_amd import bta
+
+    prev = bta.gemm_mode(mode)
+    try:
+        test_selinv_product_by_product(torch_cuda, n, b, a)
+    finally:
+        bta.gemm_mode(prev)
+
+
 def test_workspace_falls_back_to_the_least(torch_cuda):
     """No room for the workspace that the selected inversion asks for: the binding
     takes the least one, and the result is the product-by-product one."""
@@ -299,6 +312,37 @@ def test_solve_chunks(torch_cuda, nrhs):
     e = float((got - x).norm() / x.norm())
     say(f"   solve rel err {e:.3e}")
     assert e < TOL
+
+
+# bit patterns: the NaN that marks a vector element as not yet written, that NaN negated, NaN, infinities
+@pytest.mark.parametrize("bits", [0x7FF8B17AB17AB17A, 0xFFF8B17AB17AB17A, 0x7FF8000000000000, 0x7FF0000000000000,
+                                  0xFFF0000000000000], ids=hex)
+@pytest.mark.parametrize("nrhs", [3, 20])
+@pytest.mark.parametrize("a", [0, 5])
+def test_solve_right_hand_side_not_finite(torch_cuda, a, nrhs, bits):
+    """Right-hand sides with NaNs and infinities, among them the value by which
+    single vectors mark elements that are pending: the call ends, every x of such a
+    right-hand side is not finite, and the other ones keep their bits."""
+    from paper_2503_17528_amd import bta
+
+    torch, n, b = torch_cuda, 4, 256
+    say(f"case solve not finite a={a} nrhs={nrhs} {bits:#x}")
+    L = bta.factor(*to_dev(synth.make_np(synth.workload(n, b, a), 3)))[:4]
+    N = n * b + a
+    y = torch.randn(N, nrhs, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    want = bta.solve(*L, y)
+    bad = y.clone()
+    w = bad.view(torch.int64)
+    v = bits - (1 << 64) if bits >> 63 else bits
+    w[0, 0] = w[b + 17, 0] = w[2 * b:2 * b + 40, 0] = w[N - 1, 0] = v  # first, inner, a run, last
+    w[N - 1, 2] = v
+    x = bta.solve(*L, bad)
+    torch.cuda.synchronize()
+    for j in range(nrhs):
+        if j in (0, 2):
+            assert not bool(x[:, j].isfinite().any()), j
+        else:
+            assert torch.equal(x[:, j], want[:, j]), j
 
 
 @pytest.mark.parametrize("n,b,a", [(6, 256, 4), (5, 193, 0), (4, 800, 70)])
