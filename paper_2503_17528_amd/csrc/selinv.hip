@@ -177,11 +177,22 @@ static int selinv_split_max(int64_t b, int64_t a) {
   return GEMM_MAX_PROBS;
 }
 
-// Largest b of the persistent sweep (us per block, a = 4, product by product
-// against the sweep): b = 384 60 / 30, 512 72 / 40, 640 102 / 71, 768 134 / 119,
-// 1024 220 / 169, 1280 333 / 305, 1536 498 / 556; odd b, with 4-byte operand
-// loads, 641 126 / 101, 1025 295 / 288.
-static int64_t sweep_max_b(int64_t b) { return b % 2 == 0 ? 1280 : 1088; }
+// Where the persistent sweep is the faster one: its rounds of 64 x 64 tiles against
+// one launch per product, with 128 x 128 tiles for the larger ones.  Whole selected
+// inversions of 32 blocks, product by product / persistent (ms): a = 4, b = 384 2.17 /
+// 1.02, 512 2.56 / 1.30, 768 4.49 / 3.79, 1024 7.03 / 5.40, 1152 8.93 / 8.60, 1280
+// 10.55 / 10.08 (200 blocks 61.9 / 62.4, 8 blocks 3.08 / 2.45), 1536 behind by 12% a
+// block; odd b, with 4-byte operand loads, 641 4.26 / 3.07, 961 7.77 / 6.58, 1025 9.30 /
+// 9.51, 1087 10.06 / 9.95 (100 blocks 29.6 / 30.5).  Wide tips, whose arrow rows fill
+// the chip in launches of their own: b = 512, a = 2048 12.7 / 9.5; 768, 2048 16.9 / 13.7;
+// 960, 3000 32.7 / 31.2; 1022, 2048 22.1 / 22.5; 1024, 1024 12.5 / 12.1; 1024, 2048 21.1 /
+// 22.1; 1152, 700 14.0 / 12.4; 1152, 2048 26.2 / 27.5; 1216, 900 17.1 / 17.4; 1280, 512
+// 13.9 / 13.9; 1280, 700 16.0 / 16.7; 1280, 1500 23.3 / 26.4; odd b 1087, 1024 18.6 / 16.9;
+// 1087, 2048 30.0 / 28.5; 1087, 4096 (16 blocks) 32.3 / 33.7.
+static bool sweep_pays(int64_t b, int64_t a) {
+  if (b % 2 != 0) return b <= 1088 && (b <= 960 || a <= 2048);
+  return b <= 1280 && a <= (b > 1152 ? 512 : b > 960 ? 1024 : INT64_MAX);
+}
 
 SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split, bool sweep) {
   SelinvPlan sp{};
@@ -205,7 +216,7 @@ SelinvPlan selinv_plan(int64_t n, int64_t b, int64_t a, bool split, bool sweep) 
   // One persistent launch for the sweep where its products are too small for
   // launches of their own, within 8 GiB for all P_B (they then have a place of
   // their own, as the sweep writes X_{i+1,i} while others still read P_B).
-  sp.sweep = sweep && split && n > 1 && b <= sweep_max_b(b) && (n - 1) * b * b <= (int64_t(8) << 30) / 8;
+  sp.sweep = sweep && split && n > 1 && sweep_pays(b, a) && (n - 1) * b * b <= (int64_t(8) << 30) / 8;
   sp.off_PB = take(sp.sweep ? 8 * bb * (size_t)(n - 1) : 8);
   sp.off_sweep = take(sp.sweep ? sweep_work_bytes(n, b, a) : 8);
   // split-k partial products of the sweep at small b (few output tiles)

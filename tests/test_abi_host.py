@@ -71,6 +71,16 @@ def test_least_workspace(bta, n, b, a):
     assert st == bta.BTA_EINVAL and "workspace too small" in bta.bta_last_error()
 
 
+@pytest.mark.parametrize("b,a,sweep", [(1280, 512, True), (1280, 513, False), (1280, 4096, False), (1152, 1024, True),
+                                       (1154, 1024, False), (1024, 2048, False), (962, 1025, False), (960, 4096, True),
+                                       (512, 4096, True), (1087, 2048, True), (1087, 2049, False), (959, 4096, True),
+                                       (1282, 4, False), (1089, 4, False)])
+def test_persistent_sweep_rule(bta, b, a, sweep):
+    """Which block and tip sizes the persistent sweep takes, by the room that it asks for."""
+    full, least = (f(bta.BTA_OP_SELINV, 16, b, a, 0) for f in (bta.bta_workspace_bytes, bta.bta_workspace_min_bytes))
+    assert (full > least) == sweep
+
+
 def test_status_strings(bta):
     for st in (bta.BTA_OK, bta.BTA_EINVAL, bta.BTA_EHIP, bta.BTA_ENOTSUP):
         assert bta.bta_status_string(st).startswith("BTA_")
