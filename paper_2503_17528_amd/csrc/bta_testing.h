@@ -124,7 +124,7 @@ BTA_TESTING_API int bta_internal_gemm(int M, int N, int K, const double* A, int6
                                       int64_t ldb, int bt, int tri, const double* Cin, double* C, int64_t ldc,
                                       double alpha, double beta, int store, int lower_tiles, hipStream_t s);
 /* nprob copies of one product (problem q offset by q*stride in A, B and C)
- * through the batched list kernel: 64 x 64 tiles with four LDS stages, or
+ * through the batched list kernel: 64 x 64 tiles with two LDS stages, or
  * 128 x 128 tiles with big; dlist is device memory of at least
  * 512 * (nprob + 1) bytes; synchronizes `s`.  -1 on a bad nprob (1..64). */
 BTA_TESTING_API int bta_internal_gemm_list(int M, int N, int K, const double* A, int64_t lda, int at, const double* B,

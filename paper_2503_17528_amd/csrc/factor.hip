@@ -329,7 +329,8 @@ __device__ __forceinline__ bool wait_ready(const FactorParams& p, const int* f1,
 
 // Wave 0: extend the run of consecutive final k tiles starting at `from`
 // without blocking.  Lane l polls the flags of k tile from + l, so one round
-// trip covers up to 64 tiles; one acquire fence covers every tile added.
+// trip covers up to 64 tiles.  Device-coherent loads need no acquire; loads through
+// the L2 (LD_LINE) get one for all the tiles added.
 __device__ __forceinline__ int extend_ready(const FactorParams& p, const Task& t, int from, int nk, int lane) {
   const int kk = from + lane;
   bool ready = false;
@@ -1673,9 +1674,9 @@ BTA_TESTING_API int bta_internal_diag_link_probe(const double* d_A, double* d_L,
 namespace bta {
 // Round-trip latency of the cross-workgroup flag hand-off: workgroup 0 and the
 // last workgroup of the grid (another XCD) pass a token `iters` times.  mode 0:
-// release store / relaxed polls + acquire fence (the factor's protocol);
-// mode 1: relaxed device-coherent store after a wait for the wave's stores,
-// relaxed polls, no fences.  ticks[0]: summed 100 MHz ticks of the round
+// release store / relaxed polls + acquire fence; mode 1 (the factor's protocol):
+// relaxed device-coherent store after a wait for the wave's stores, relaxed
+// polls, no fences.  ticks[0]: summed 100 MHz ticks of the round
 // trips measured by workgroup 0.
 __global__ __launch_bounds__(64) void flag_pingpong_kernel(int* flags, long long* ticks, int iters, int mode) {
   const bool a = blockIdx.x == 0, b = blockIdx.x == gridDim.x - 1;

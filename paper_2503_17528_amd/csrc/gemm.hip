@@ -56,7 +56,7 @@ __device__ __align__(16) double g_zero_piece[2] = {0.0, 0.0};
 
 // ---------------------------------------------------------------- lean direct-to-LDS tile body
 // Waves WR x WC, each (16 BI) x (16 BJ) of the (16 BI WR) x (16 BJ WC) tile;
-// stages of BK = 16 as in gemm_tile_dl (same piece layouts).  The loads of 64 x
+// stages of BK = 16 laid out as gemm_stage.hpp says.  The loads of 64 x
 // 64 tiles and of U go through stage_pieces; those of 128 x 128 tiles keep a
 // pointer per piece (registers are free there, one workgroup per CU, and the
 // scalar row bases measured slower: n=32, b=4096 321.9 against 329.2 ms).

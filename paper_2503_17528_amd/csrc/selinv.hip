@@ -11,8 +11,10 @@
 // L_ii, with each solve replaced by the product with W_i (the paper's own
 // substitution of repeated TRSMs by one inversion plus GEMMs).  W_i, P_i and
 // V_i = W_i^T W_i depend on the factor only, so they are computed for all
-// blocks up front in large batched launches (chunks of blocks); the
-// sequential backward sweep is then two MFMA GEMM launches per step.
+// blocks up front in large batched launches (chunks of blocks).  The sequential
+// backward sweep of small blocks is one persistent launch behind them
+// (sweep.hip; sweep_pays says where); that of larger ones, or in a workspace with
+// no room for every P_B, is two MFMA GEMM launches per step, as follows.
 //   X_{n,n} = L_nn^{-T} L_nn^{-1} comes from the same inverse + product.
 //
 // The arrow rows form a recursion of their own, X_{n,i} = -(X_{n,i+1} P_B +

@@ -193,20 +193,17 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// out[r] = base[r] + sign * sum_k M[r*ld + k] x[k] for the rows of this
-// workgroup, batched over blockIdx.y (right-hand sides) and blockIdx.z
-// (independent blocks).  tri = 0: k < K; tri = 1 (lower triangular M): only
-// k < r0 + rows of the workgroup are read; tri = 2 (upper): only k >= r0.
-// Elements of a triangular M outside its triangle must be zero.  base may be
-// null (out = sign * sum) and M may be null (K = 0: out = base).
+// out[r] = sum_k M[r*ld + k] x[k] for the rows of this workgroup, batched over
+// blockIdx.y (right-hand sides) and blockIdx.z (independent blocks).  tri = 0:
+// k < K; tri = 1 (lower triangular M): only k < r0 + rows of the workgroup are
+// read; tri = 2 (upper): only k >= r0.  Elements of a triangular M outside its
+// triangle must be zero.
 struct MvArgs {
   const double* M; int64_t ld, sMz;
   const double* x; int64_t sxy, sxz;
-  const double* base; int64_t sby, sbz;
   double* out; int64_t soy, soz;
   int64_t rows, K;
   int tri;
-  double sign;
 };
 
 // Wave w takes RPW consecutive rows; its lanes run along k in 64-wide chunks,
@@ -225,7 +222,7 @@ __global__ __launch_bounds__(256) void matvec_rows_kernel(MvArgs p) {
   double s[RPW];
 #pragma unroll
   for (int j = 0; j < RPW; ++j) s[j] = 0.0;
-  if (p.M != nullptr && k1 > k0) {
+  if (k1 > k0) {
     const double* M = p.M + z * p.sMz;
     const double* x = p.x + y * p.sxy + z * p.sxz;
     int64_t roff[RPW];
@@ -256,10 +253,7 @@ __global__ __launch_bounds__(256) void matvec_rows_kernel(MvArgs p) {
   for (int j = 0; j < RPW; ++j) {
     const double t = wave_sum(s[j]);
     const int64_t r = rw + j;
-    if (lane == 0 && r < p.rows) {
-      const double b0 = p.base ? p.base[y * p.sby + z * p.sbz + r] : 0.0;
-      p.out[y * p.soy + z * p.soz + r] = b0 + p.sign * t;
-    }
+    if (lane == 0 && r < p.rows) p.out[y * p.soy + z * p.soz + r] = t;
   }
 }
 
@@ -790,7 +784,7 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
       pp.M = LR; pp.ld = b; pp.sMz = ab;
       pp.x = z; pp.sxy = N; pp.sxz = b;
       pp.out = ptip; pp.soy = n * a; pp.soz = a;
-      pp.rows = a; pp.K = b; pp.tri = 0; pp.sign = 1.0;
+      pp.rows = a; pp.K = b; pp.tri = 0;
       BTA_TRY_E(matvec_rows(pp, nr, (int)n, stream));
     } else {
       const dim3 g((unsigned)((a + TIP_ROWS - 1) / TIP_ROWS), (unsigned)n, (unsigned)sp.NG);
@@ -807,13 +801,13 @@ hipError_t solve_launch(int64_t n, int64_t b, int64_t a, const double* LD, const
     fz.M = WT; fz.ld = a;
     fz.x = t2; fz.sxy = a;
     fz.out = tb; fz.soy = a;
-    fz.rows = a; fz.K = a; fz.tri = 1; fz.sign = 1.0;
+    fz.rows = a; fz.K = a; fz.tri = 1;
     BTA_TRY_E(matvec_rows(fz, nr, 1, stream));
     MvArgs bx{};
     bx.M = WTt; bx.ld = a;
     bx.x = tb; bx.sxy = a;
     bx.out = xn; bx.soy = a;
-    bx.rows = a; bx.K = a; bx.tri = 2; bx.sign = 1.0;
+    bx.rows = a; bx.K = a; bx.tri = 2;
     BTA_TRY_E(matvec_rows(bx, nr, 1, stream));
   }
   if (a > 0 || sp.npend > 0) {

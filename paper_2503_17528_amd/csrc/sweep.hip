@@ -10,7 +10,8 @@
 // workgroup: at b = 512 a phase A is 256 tasks, one per CU, where 64 x 64 tiles
 // would be 64.  Launched product by product, a step of b = 512 took 68 us (four
 // launches on the chain besides the copy and the arrow row); here it is two
-// waits, 30 us, bound by reading the operands (64 MB of tiles a phase A).  Taking
+// waits, 30 us (both without W, P and V: 9 us a block), bound by reading the
+// operands (64 MB of tiles a phase A).  Taking
 // the next ticket while a task runs left ready tasks with busy workgroups (n=256,
 // b=512: 17.1 ms against 10.0).
 //
