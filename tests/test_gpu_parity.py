@@ -138,30 +138,32 @@ def test_selinv_product_by_product_kernels(torch_cuda, n, b, a, mode):
         bta.gemm_mode(prev)
 
 
-def test_workspace_falls_back_to_the_least(torch_cuda):
+def test_workspace_falls_back_to_the_least(torch_cuda, monkeypatch):
     """No room for the workspace that the selected inversion asks for: the binding
-    takes the least one, and the result is the product-by-product one."""
+    takes the least one, and the result is the product-by-product one; a call with
+    nothing smaller to fall back to raises."""
     from paper_2503_17528_amd import bta
 
-    torch, n, b, a = torch_cuda, 200, 256, 4
+    torch, n, b, a = torch_cuda, 20, 256, 4
     say(f"case workspace fallback n={n} b={b} a={a}")
     L = bta.factor(*to_dev(synth.make_np(synth.workload(n, b, a), 2)))[:4]
     full, least = (f(bta.BTA_OP_SELINV, n, b, a) for f in (bta.bta_workspace_bytes, bta.bta_workspace_min_bytes))
     out = [torch.empty_like(t) for t in L]
     want = bta.selinv(*L, work=torch.empty(least, dtype=torch.uint8, device="cuda"))
-    torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    total = torch.cuda.get_device_properties(0).total_memory
-    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (full + least) // 2) / total)
-    try:
-        work, nbytes = bta.workspace(bta.BTA_OP_SELINV, n, b, a, "cuda")
-        assert nbytes == work.numel() == least
-        del work
-        bta.selinv(*L, out=out)
-        with pytest.raises(torch.OutOfMemoryError):  # nothing smaller to fall back to
-            bta.workspace(bta.BTA_OP_SOLVE, 4000, b, a, "cuda", 64)
-    finally:
-        torch.cuda.set_per_process_memory_fraction(1.0)
+    real = torch.empty
+
+    def no_room(*size, **kw):
+        if kw.get("dtype") == torch.uint8 and size[0] > least:
+            raise torch.OutOfMemoryError("no room")
+        return real(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", no_room)
+    work, nbytes = bta.workspace(bta.BTA_OP_SELINV, n, b, a, "cuda")
+    assert nbytes == work.numel() == least < full
+    bta.selinv(*L, out=out)
+    with pytest.raises(torch.OutOfMemoryError):
+        bta.workspace(bta.BTA_OP_SOLVE, 400, b, a, "cuda", 64)
+    monkeypatch.undo()
     for x, y in zip(out, want):
         assert torch.equal(x, y)
 
