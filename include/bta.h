@@ -79,10 +79,11 @@ typedef enum {
 BTA_API size_t bta_workspace_bytes(int op, int64_t n, int64_t b, int64_t a, int64_t nrhs);
 
 /* The least workspace that `op` accepts: bta_workspace_bytes, except that
- * bta_selinv of small blocks (b <= 1280, odd b <= 1088) also runs without the
- * 8 (n-1) b^2 bytes, at most 8 GiB, that hold the products L_{i+1,i} L_ii^{-1}
- * of all blocks for its persistent backward sweep.  It then sweeps product by
- * product (b = 512: about twice the time). */
+ * bta_selinv of small blocks (b <= 1280, odd b <= 1088; above b = 960 with tips up
+ * to a = 512 to 2048 only) also runs without the 8 (n-1) b^2 bytes, at most 8 GiB,
+ * that hold the products L_{i+1,i} L_ii^{-1} of all blocks for its persistent
+ * backward sweep.  It then sweeps product by product (b = 512: about twice the
+ * time). */
 BTA_API size_t bta_workspace_min_bytes(int op, int64_t n, int64_t b, int64_t a, int64_t nrhs);
 
 /*
